@@ -349,13 +349,17 @@ lindhard_status plan_describe(const lindhard_problem *p, Plan &pl)
             for (int iy = 0; iy < ny; ++iy)
                 for (int ix = 0; ix < nx; ++ix) {
                     const double e = tab[(size_t)iy * nx + ix];
-                    if (e != tab[(size_t)iy * nx + ((nx - ix) & (nx - 1))] ||
-                        e != tab[(size_t)((ny - iy) & (ny - 1)) * nx + ix])
+                    if (e != tab[(size_t)iy * nx + (ix ? nx - ix : 0)] ||
+                        e != tab[(size_t)(iy ? ny - iy : 0) * nx + ix])
                         return false;
                 }
             return true;
         };
-        if (nkz > 1 || g.bs) sym = false;  // the real even form: two dimensions, powers of two
+        if (nkz > 1) sym = false;  // the real even form: two dimensions
+        // sizes that are not powers of two: even convolutions of at most 4096
+        // points (sizes up to 2049; longer lines would not fit twice in a CU's LDS)
+        const int evx = std::max(8, ilog2(4 * (p->nkx / 2))), evy = std::max(8, ilog2(4 * (p->nky / 2)));
+        if (g.bs && (evx > 12 || evy > 12)) sym = false;
         for (int b = 0; b < nbands && sym; ++b) {
             if (p->eps_table) sym = mirror(p->eps_table + b * nk);
             if (sym && p->rho_table) sym = mirror(p->rho_table + b * nk);
@@ -363,6 +367,10 @@ lindhard_status plan_describe(const lindhard_problem *p, Plan &pl)
         if (const char *ev = std::getenv("LINDHARD_SYMMETRY"))
             if (!std::strcmp(ev, "off")) sym = false;
         g.even = sym ? 1 : 0;
+        if (g.bs && g.even) {
+            g.logMx = evx;
+            g.logMy = evy;
+        }
         const size_t es = g.fp64 ? 8 : 4;
         g.Ce = (int)(32 / es);
         g.logCe = ilog2(g.Ce);
@@ -518,6 +526,7 @@ std::vector<BufSpec> plan_buffers(const Plan &cpl)
     const size_t sl = g.even ? g.slice_e * es : g.slice_elems * cs;  // bytes per slice
     const bool pair_ws = pl.pairs && g.nL > 0, rpa = pl.p.want_rpa != 0;
     const bool band_ws = (pl.pairs || (pl.has_m2 && pl.nb > 1)) && g.nL > 0;  // per-band spectra
+    const bool bse = g.bs && g.even;
     const size_t Mx = g.bs ? ((size_t)1 << g.logMx) * cs : 0, My = g.bs ? ((size_t)1 << g.logMy) * cs : 0;
     const size_t nw = (size_t)pl.p.nomega;
     return {
@@ -530,8 +539,12 @@ std::vector<BufSpec> plan_buffers(const Plan &cpl)
         {&pl.twz, g.nkz * cs},
         {&pl.bsx[0], g.bs ? g.nkx * cs : 0},
         {&pl.bsy[0], g.bs ? g.nky * cs : 0},
-        {&pl.bsx[1], Mx}, {&pl.bsx[2], Mx}, {&pl.bsx[3], Mx},
-        {&pl.bsy[1], My}, {&pl.bsy[2], My}, {&pl.bsy[3], My},
+        {&pl.bsx[1], bse ? even_any_spectrum_len(g.logMx) * cs : Mx},
+        {&pl.bsx[2], bse ? even_any_twiddle_len(g.logMx) * cs : Mx},
+        {&pl.bsx[3], bse ? 0 : Mx},
+        {&pl.bsy[1], bse ? even_any_spectrum_len(g.logMy) * cs : My},
+        {&pl.bsy[2], bse ? even_any_twiddle_len(g.logMy) * cs : My},
+        {&pl.bsy[3], bse ? 0 : My},
         {&pl.twe, ((size_t)1 << g.logNE) * cs},
         {(void **)&pl.ffx, (size_t)pl.out_nx * 16},
         {(void **)&pl.ffy, (size_t)pl.out_ny * 16},
@@ -988,54 +1001,76 @@ static void fft_host(std::vector<std::complex<double>> &a)
     }
 }
 
+// One table of complex values times sc, rounded once to the plan's precision,
+// to the device.  `keep` holds the host array until the copy has run.
+static hipError_t put_table(const Plan &pl, const std::vector<std::complex<double>> &v, double sc, void *dst,
+                            hipStream_t st, std::vector<std::vector<double>> &keep)
+{
+    const size_t nv = 2 * v.size();  // interleaved (re, im)
+    // (FP32 pairs are packed into the storage of nv / 2 doubles)
+    keep.emplace_back(pl.g.fp64 ? nv : nv / 2);
+    double *hd = keep.back().data();
+    float *hf = reinterpret_cast<float *>(hd);
+    for (size_t k = 0; k < v.size(); ++k) {
+        const double re = v[k].real() * sc, im = v[k].imag() * sc;
+        if (pl.g.fp64) {
+            hd[2 * k] = re;
+            hd[2 * k + 1] = im;
+        } else {
+            hf[2 * k] = (float)re;
+            hf[2 * k + 1] = (float)im;
+        }
+    }
+    return hipMemcpyAsync(dst, hd, nv * (pl.g.fp64 ? sizeof(double) : sizeof(float)), hipMemcpyHostToDevice, st);
+}
+
 // Bluestein tables of one axis of length n (a grid of any size): chirp
 // b_k = exp(i pi (k^2 mod 2n) / n), the spectra FFT_M(B) / M and FFT_M(conj B) / M
 // of the chirp sequence B (B_m = b_m = B_(M-m) for m < n, zero between; with
 // M = 2n - 2 the place n - 1 serves both m = n - 1 and m = -(n - 1)), and
 // the FFT twiddles exp(-2 pi i s / M); FP64, rounded once to the precision.
-// `keep` holds the host arrays until the copies have run.
+// The even path takes the chirp for k <= n / 2, B_m for m <= 2 floor(n / 2)
+// (centred indices; M >= 4 floor(n / 2)), one spectrum (the forward and inverse
+// transforms of even sequences are the same) and twiddles in EvenFFT's order.
 static hipError_t bs_tables(const Plan &pl, int n, int logM, void *const *dst, hipStream_t st,
                             std::vector<std::vector<double>> &keep)
 {
+    using cd = std::complex<double>;
     const size_t M = (size_t)1 << logM;
-    std::vector<std::complex<double>> b(n), B(M, 0.0), Bc(M, 0.0), tw(M);
-    for (int k = 0; k < n; ++k) {
+    const int nb = pl.g.even ? 2 * (n / 2) + 1 : n;
+    std::vector<cd> b(nb), B(M, 0.0), tw(M);
+    for (int k = 0; k < nb; ++k) {
         const double ang = M_PI * (double)(((long)k * k) % (2L * n)) / (double)n;
-        b[k] = std::complex<double>(std::cos(ang), std::sin(ang));
+        b[k] = cd(std::cos(ang), std::sin(ang));
     }
-    for (int m = 0; m < n; ++m) {
+    for (int m = 0; m < nb; ++m) {
         B[m] = b[m];
         if (m > 0) B[M - m] = b[m];
     }
+    for (size_t s = 0; s < M; ++s) {
+        const double ang = -2.0 * M_PI * (double)s / (double)M;
+        tw[s] = cd(std::cos(ang), std::sin(ang));
+    }
+    const double inv = 1.0 / (double)M;
+    if (pl.g.even) {
+        fft_host(B);
+        std::vector<cd> h(even_any_spectrum_len(logM)), t(even_any_twiddle_len(logM));
+        for (size_t e = 0; e < h.size(); ++e) h[e] = B[even_any_spectrum_index(logM, e) & (M - 1)];
+        for (size_t e = 0; e < t.size(); ++e) t[e] = tw[even_any_twiddle_index(logM, e) & (M - 1)];
+        b.resize(n / 2 + 1);
+        hipError_t e = put_table(pl, b, 1.0, dst[0], st, keep);
+        if (e == hipSuccess) e = put_table(pl, h, inv, dst[1], st, keep);
+        if (e == hipSuccess) e = put_table(pl, t, 1.0, dst[2], st, keep);
+        return e;
+    }
+    std::vector<cd> Bc(M);
     for (size_t m = 0; m < M; ++m) Bc[m] = std::conj(B[m]);
     fft_host(B);
     fft_host(Bc);
-    for (size_t s = 0; s < M; ++s) {
-        const double ang = -2.0 * M_PI * (double)s / (double)M;
-        tw[s] = std::complex<double>(std::cos(ang), std::sin(ang));
-    }
-    const std::vector<std::complex<double>> *src[4] = {&b, &B, &Bc, &tw};
-    const double sc[4] = {1.0, 1.0 / (double)M, 1.0 / (double)M, 1.0};
+    const std::vector<cd> *src[4] = {&b, &B, &Bc, &tw};
+    const double sc[4] = {1.0, inv, inv, 1.0};
     for (int i = 0; i < 4; ++i) {
-        const auto &v = *src[i];
-        const size_t nv = 2 * v.size();  // interleaved (re, im)
-        // one host array per table, in the plan's precision (FP32 pairs are
-        // packed into the storage of nv / 2 doubles)
-        keep.emplace_back(pl.g.fp64 ? nv : nv / 2);
-        double *hd = keep.back().data();
-        float *hf = reinterpret_cast<float *>(hd);
-        for (size_t k = 0; k < v.size(); ++k) {
-            const double re = v[k].real() * sc[i], im = v[k].imag() * sc[i];
-            if (pl.g.fp64) {
-                hd[2 * k] = re;
-                hd[2 * k + 1] = im;
-            } else {
-                hf[2 * k] = (float)re;
-                hf[2 * k + 1] = (float)im;
-            }
-        }
-        const hipError_t e = hipMemcpyAsync(dst[i], hd, nv * (pl.g.fp64 ? sizeof(double) : sizeof(float)),
-                                            hipMemcpyHostToDevice, st);
+        const hipError_t e = put_table(pl, *src[i], sc[i], dst[i], st, keep);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -83,6 +83,8 @@ struct Geo {
     // 2^logMy; bs_Rr rows per block in the row passes, bs_Rc columns per
     // block in the column passes, bs_SJ energy slices (or lags) per block in
     // the column passes
+    // (with even = 1: chirp convolutions of even sequences, lh_even_any.hip, of
+    // length 2^logMx, 2^logMy in 256 .. 4096)
     int bs, logMx, logMy, bs_Rr, bs_Rc, bs_SJ;
 };
 
@@ -127,6 +129,7 @@ struct Plan {
     void *twy = nullptr;       // cx<T>[nky]
     void *twz = nullptr;       // cx<T>[nkz] (three dimensions)
     // grids of any size: per axis chirp b, chirp spectra hf / hi, FFT twiddles of length M
+    // (even path: chirp, spectrum and twiddles in EvenFFT's order)
     void *bsx[4] = {nullptr, nullptr, nullptr, nullptr};
     void *bsy[4] = {nullptr, nullptr, nullptr, nullptr};
     void *twe = nullptr;       // cx<T>[2^logNE] (energy-axis FFT)
@@ -220,6 +223,13 @@ hipError_t launch_window(const Plan &pl, hipStream_t st);  // energy-window pass
 // The even window as 4 x 4 rank-1 matrix updates (FP32), W waves per block.
 size_t e3q_lds_bytes(const Geo &g, int W);
 hipError_t launch_e3q(const Plan &pl, int W, hipStream_t st);
+// The mirror-symmetric path on grids of any size: pass 1, 2, 4 or 5, and the
+// order of its per-axis tables.
+hipError_t launch_even_any(const Plan &pl, int pass, void *out, hipStream_t st);
+size_t even_any_spectrum_len(int logM);
+size_t even_any_spectrum_index(int logM, size_t e);
+size_t even_any_twiddle_len(int logM);
+size_t even_any_twiddle_index(int logM, size_t e);
 hipError_t launch_cut(const Plan &pl, const void *im, const int *xy, int npts, void *out, hipStream_t st);
 // res: 3 + 4 * nseg doubles of device memory; im_plane: the plane to cut
 hipError_t launch_envelope(const Plan &pl, const void *im_plane, int dir, int W, int nseg, double qstep, double *res,

@@ -12,8 +12,7 @@
 //       factor |M(Q)|^2 (Eqs. (2)-(3)) and extended-zone writes
 // RPA path (Sec. 4): P5 keeps every lag of the first zone, then the
 // Kramers-Kronig and chi / (1 - U chi) epilogues.
-#include "lh_fft.h"
-#include "lh_internal.h"
+#include "lh_device.h"
 #include "lh_regfft.h"
 
 #include <map>
@@ -21,7 +20,6 @@
 
 namespace lh {
 
-constexpr double kPi = 3.14159265358979323846;
 constexpr int kThreads = 256;
 
 // ---------------------------------------------------------------- setup
@@ -152,13 +150,6 @@ __global__ void __launch_bounds__(kThreads) k_kkw(double *__restrict__ w, const 
     w[idx] = (lag >= 0 && j < neps) ? kk_weight(lag, j) : 0.0;
 }
 
-// 16 bytes of consecutive elements (one vector load or store per lane).
-template <typename T>
-struct Vec16 {
-    T v[16 / sizeof(T)];
-};
-typedef unsigned lh_u4 __attribute__((ext_vector_type(4)));
-
 // Blocks are dispatched round-robin over the 8 XCDs (each with its own L2).
 // Map launch index b to a logical tile so that consecutive logical tiles run
 // on the same XCD: tiles sharing cache lines then meet in the same L2.
@@ -167,23 +158,6 @@ __device__ __forceinline__ unsigned xcd_tile(unsigned b, unsigned nblocks)
     const unsigned per = nblocks >> 3;          // full rounds of 8
     if (b >= (per << 3)) return b;              // ragged tail keeps its index
     return (b & 7) * per + (b >> 3);
-}
-
-// Lorentzian of Eq. (5) from the (already rounded) argument d = e_j - xi_k:
-// (gamma/pi) / (d^2 + gamma^2).  FP32 uses the hardware reciprocal (1 ulp).
-__device__ __forceinline__ float lorentz(float d, float gp, float g2)
-{
-    return gp * __builtin_amdgcn_rcpf(d * d + g2);
-}
-__device__ __forceinline__ double lorentz(double d, double gp, double g2) { return gp / (d * d + g2); }
-
-// |M(Q)|^2 = F(Q)^2 at extended (X, Y), Eq. (3) for the Gaussian d orbital.
-__device__ __forceinline__ double form_factor_sq(const double2 fx, const double2 fy, double s)
-{
-    const double q2 = fx.y + fy.y;
-    const double dq = fx.y - fy.y;
-    const double F = fx.x * fy.x * (1.0 - 2.0 * s * q2 + s * s * dq * dq);
-    return F * F;
 }
 
 // FP32: an FFT twiddle table of n values copied into LDS at dst (stored with
@@ -2163,26 +2137,6 @@ struct BsTab {
     int n;
 };
 
-// Launch index -> work index such that grp consecutive work items (which
-// share cache lines) run on one XCD: blocks are dispatched round-robin over the
-// 8 XCDs, launch index b on XCD b mod 8.  The grid is padded to a multiple of
-// 8 grp blocks; the caller skips work indices past its range.
-__device__ __forceinline__ int xcd_group(int b, int grp)
-{
-    const int xcd = b & 7, i = b >> 3;
-    return ((i / grp) * 8 + xcd) * grp + i % grp;
-}
-
-// A zero the optimiser cannot see through.  Added to a thread's position in
-// a loop body it keeps the loads and LDS addresses that depend on it inside
-// the loop, rather than hoisted out and held in registers across it.
-__device__ __forceinline__ int opaque_zero()
-{
-    int z = 0;
-    asm volatile("" : "+s"(z));
-    return z;
-}
-
 // FP32 up to M = 4096: the FFT twiddles of an axis copied into LDS after the
 // block's R line buffers (M values), so that every pass reads them from LDS
 // rather than waiting on the cache.  FP64 and longer lines keep them in
@@ -2749,7 +2703,8 @@ static void launch_bs_p5(const Plan &pl, const cx<T> *spec, T *out, hipStream_t 
                        pl.d_src, pl.scale, out, pl.zx, pl.zy, ff, pl.ff_s, pl.ffx, pl.ffy);
 }
 
-// Grids of any size: Bluestein row and column passes around the same window.
+// Grids of any size: Bluestein row and column passes around the same window
+// (mirror-symmetric bands: the passes of lh_even_any.hip and the even window).
 template <typename T>
 static hipError_t exec_bs(const Plan &pl, T *out, hipStream_t st, hipEvent_t *ev)
 {
@@ -2759,7 +2714,16 @@ static hipError_t exec_bs(const Plan &pl, T *out, hipStream_t st, hipEvent_t *ev
         if (ev) (void)hipEventRecord(ev[i], st);
     };
     mark(0);
-    if (g.nL > 0) {
+    if (g.nL > 0 && g.even) {
+        LH_HIP_TRY(launch_even_any(pl, 1, nullptr, st));
+        mark(1);
+        LH_HIP_TRY(launch_even_any(pl, 2, nullptr, st));
+        mark(2);
+        LH_HIP_TRY(window_t<T>(pl, st));
+        mark(3);
+        LH_HIP_TRY(launch_even_any(pl, 4, nullptr, st));
+        mark(4);
+    } else if (g.nL > 0) {
 #define LH_B1(LG) launch_bs_row<T, LG>(pl, spec, st)
         LH_SWITCH_LOGM(g.logMx, LH_B1)
 #undef LH_B1
@@ -2782,7 +2746,9 @@ static hipError_t exec_bs(const Plan &pl, T *out, hipStream_t st, hipEvent_t *ev
     }
     if (pl.p.want_rpa) {
         // the RPA path: first-zone maps of every lag, then the requested planes
-        if (g.nL > 0) {
+        if (g.nL > 0 && g.even) {
+            LH_HIP_TRY(launch_even_any(pl, 5, nullptr, st));
+        } else if (g.nL > 0) {
 #define LH_B5(LG) launch_bs_p5<T, LG, 1>(pl, spec, (T *)pl.im1, st)
             LH_SWITCH_LOGM(g.logMx, LH_B5)
 #undef LH_B5
@@ -2791,6 +2757,8 @@ static hipError_t exec_bs(const Plan &pl, T *out, hipStream_t st, hipEvent_t *ev
         hipLaunchKernelGGL(k_extend<T>, dim3(cdiv(g.nkx, kThreads), g.nky, cdiv(pl.p.nomega, 4)), dim3(kThreads), 0,
                            st, (const T *)pl.im1, g.nkx, g.nky, 1, g.neps, pl.d_lag, pl.d_frac, pl.p.nomega, pl.zx,
                            pl.zy, ff, pl.ff_s, pl.ffx, pl.ffy, out, pl.out_nx, pl.out_ny);
+    } else if (g.even) {
+        LH_HIP_TRY(launch_even_any(pl, 5, out, st));
     } else {
 #define LH_B5(LG) launch_bs_p5<T, LG, 0>(pl, spec, out, st)
         LH_SWITCH_LOGM(g.logMx, LH_B5)
