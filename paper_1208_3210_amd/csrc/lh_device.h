@@ -51,6 +51,43 @@ __device__ __forceinline__ int xcd_group(int b, int grp)
     return ((i / grp) * 8 + xcd) * grp + i % grp;
 }
 
+// Where a run of the window's points lies: element offset p in the slice, and
+// with the exchange symmetry (g.sw) the tile t and row r of the first point.
+struct WinRun {
+    size_t p;
+    int t, r;
+};
+// Points a window pass runs on.
+__host__ __device__ __forceinline__ size_t win_points(const Geo &g)
+{
+    return g.sw ? (size_t)g.sw_units * 4 * g.Ce : g.slice_e;
+}
+// The run that starts at point i (runs of a power of two of at most 4 Ce points
+// that start at a multiple of their length do not leave one unit).
+__device__ __forceinline__ WinRun win_run(const Geo &g, size_t i)
+{
+    if (!g.sw) return WinRun{i, 0, 0};
+    // unit u -> tile t: the units before tile t are A t - c t (t - 1) / 2
+    const int ue = 4 * g.Ce, u = (int)(i / ue), e = (int)(i % ue), A = g.sw_A, c = g.Ce / 4;
+    auto base = [&](int t) { return A * t - c * (t * (t - 1) / 2); };
+    const float b = (float)(2 * A + c);
+    int t = (int)((b - sqrtf(fmaxf(b * b - 8.0f * c * (float)u, 0.0f))) / (float)(2 * c));
+    t = min(max(t, 0), g.NTe - 1);
+    while (t + 1 < g.NTe && base(t + 1) <= u) ++t;
+    while (t > 0 && base(t) > u) --t;
+    const int r = g.Ce * t + 4 * (u - base(t)) + e / g.Ce;
+    return WinRun{((size_t)t * g.HyS + r) * g.Ce + e % g.Ce, t, r};
+}
+// Element offset of the exchanged point of (tile t, row r, column c of the
+// tile), or -1 where there is none to write (the tile's own diagonal block holds
+// both; padding).
+__device__ __forceinline__ long win_mirror(const Geo &g, int t, int r, int c)
+{
+    const int rx = t * g.Ce + c, t2 = r >> g.logCe;
+    if (!g.sw || t2 <= t || rx > g.L || r >= g.Hy) return -1;
+    return ((long)t2 * g.HyS + rx) * g.Ce + (r & (g.Ce - 1));
+}
+
 // LDS written by some lanes of a wave is read by others of the same wave: the
 // LDS serves one wave's accesses in order, so only the compiler has to keep
 // them so.

@@ -243,10 +243,11 @@ __global__ void __launch_bounds__((ev_threads<T, LOGM>()), (sizeof(T) == 4 ? 6 :
 // complex value per row), the lines of a tile interleaved lane by lane so that
 // a wave's loads and stores cover whole tile rows.  In place, one slice at a
 // time for sj slices, streamed past the L1, which holds the tables (2.96 -> 2.47
-// ms at 2049^2 x 512).
+// ms at 2049^2 x 512).  upper: only the rows ry >= Ce tile are stored (the forward
+// pass with the exchange symmetry).
 template <typename T, int LOGM>
 __global__ void __launch_bounds__((ev_threads<T, LOGM>()), (sizeof(T) == 4 ? 6 : 3))
-    k_becol(T *__restrict__ spec, Geo g, EvTab ty, int nslices, int sj)
+    k_becol(T *__restrict__ spec, Geo g, EvTab ty, int nslices, int sj, int upper)
 {
     using F = EvenFFT<T, LOGM>;
     constexpr int L = ev_lines<T, LOGM>(), LS = ev_stride<T, LOGM>(true), C = 16 / sizeof(T);
@@ -258,7 +259,7 @@ __global__ void __launch_bounds__((ev_threads<T, LOGM>()), (sizeof(T) == 4 ? 6 :
     const int line2 = tid / F::TL, q2 = tid % F::TL;       // length-P transforms
     const int tile = blockIdx.x * (L / C) + line / C, c = line % C;
     const bool act = q <= F::P / 2 && tile < g.NTe;
-    const int H = g.nky / 2;
+    const int H = g.nky / 2, nlo = upper ? tile * g.Ce : 0;
     ev_fill_t2<T, LOGM>(t2, ty, tid);
     const int s0 = blockIdx.y * sj, s1 = min(nslices, s0 + sj);
     for (int s = s0; s < s1; ++s) {
@@ -277,7 +278,7 @@ __global__ void __launch_bounds__((ev_threads<T, LOGM>()), (sizeof(T) == 4 ? 6 :
 #pragma unroll
             for (int i = 0; i < kNz; ++i) {
                 const int n = ev_index<F::P>(i, qo);
-                if (n <= H) store_nt(at32(base, o0 + n * C), x[i]);
+                if (n <= H && n >= nlo) store_nt(at32(base, o0 + n * C), x[i]);
             }
         }
         __syncthreads();
@@ -439,7 +440,7 @@ hipError_t pass_t(const Plan &pl, int pass, void *out, hipStream_t st)
         const unsigned nx = cdiv(g.NTe, TB);                                                                         \
         const int sj = (int)std::max(1L, std::min(4L, (long)nx * n / 2048));                                         \
         hipLaunchKernelGGL((k_becol<T, LG>), dim3(nx, cdiv(n, sj)), dim3(ev_threads<T, LG>()), (ev_lds<T, LG>(true)), \
-                           st, spec, g, ev_tab(pl, true), n, sj);                                                    \
+                           st, spec, g, ev_tab(pl, true), n, sj, pass == 2 && g.sw);                                                    \
     } while (0)
         LH_EV_SWITCH(g.logMy, LH_BEC)
 #undef LH_BEC

@@ -55,6 +55,13 @@ struct Geo {
     int Ce, logCe, NTe, Hy;
     int HyS;                  // row stride of a tile: Hy rounded up to 4 rows (128 bytes)
     size_t slice_e;
+    // band symmetric under the exchange of kx and ky (sw = 1, nkx = nky): the
+    // functions are symmetric in rx, ry, so the window runs on the points with
+    // ry >= Ce (rx / Ce) only (whole tile rows), in sw_units units of four rows
+    // (128 bytes), sw_A of them in tile 0 and Ce / 4 fewer in each next tile,
+    // and writes each result to both places; the forward column pass stores
+    // those rows only
+    int sw, sw_A, sw_units;
     int e1_R, e1_jc;          // row pairs per block, slices per block
     int e3_TR, e3_logTR;      // real-space points per block, even window
     int e3_PL;                // padded length of each reversed / shifted window array

@@ -30,14 +30,15 @@ __global__ void __launch_bounds__(kThreads) k_band_tb(double *__restrict__ eps, 
     const long k = (long)blockIdx.x * kThreads + threadIdx.x;
     if (k >= nk) return;
     // folded indices make eps(kx, ky) = eps(-kx, ky) = eps(kx, -ky) bit for bit
-    // (any grid size: the row index by division)
+    // (any grid size: the row index by division), and sums and products of the
+    // two axes' terms taken first make eps(kx, ky) = eps(ky, kx) so
     const int kx0 = (int)(k % nkx), ky0 = (int)(k / nkx);
     const int ix = min(kx0, nkx - kx0);
     const int iy = min(ky0, nky - ky0);
     // k_zones kz: the grid spans kz zones, k = 2 pi kz (ix / nkx, iy / nky)
     const double cx = cospi(2.0 * kz * ix / nkx), cy = cospi(2.0 * kz * iy / nky);
     const double c2x = cospi(4.0 * kz * ix / nkx), c2y = cospi(4.0 * kz * iy / nky);
-    eps[k] = -2.0 * t * (cx + cy) - 4.0 * tp * cx * cy - 2.0 * tpp * (c2x + c2y);
+    eps[k] = -2.0 * t * (cx + cy) - 4.0 * tp * (cx * cy) - 2.0 * tpp * (c2x + c2y);
 }
 
 // Partial sums of the occupation n(mu) and of dn/dmu over a fixed grid-stride
@@ -916,7 +917,8 @@ __device__ __forceinline__ void ecol_body(T *__restrict__ spec, const Geo &g,
 #pragma unroll
         for (int s = 0; s < E; ++s) {
             const int ry = gg + s * G;
-            if (ry < Hy) base[ry * C + c] = v[s];
+            // (exchange symmetry: the window reads the rows ry >= Ce tile only)
+            if (ry < Hy && (INV || !g.sw || ry >= tile * 2 * C)) base[ry * C + c] = v[s];
         }
     }
 }
@@ -960,7 +962,10 @@ __device__ __forceinline__ void e3_body(T *__restrict__ spec, const Geo &g)
     T *Pz = lds;                    // [PL][TR]
     T *Hz = lds + (size_t)PL * TR;  // [HP + HL][TR], row (HP + x)
     const int tid = threadIdx.x;
-    const size_t p0 = (size_t)xcd_tile(blockIdx.x, gridDim.x) * TR;
+    // this thread's point (the same in every staging step: TR divides the block)
+    const size_t pi = (size_t)xcd_tile(blockIdx.x, gridDim.x) * TR + tid % TR, np = win_points(g);
+    const WinRun run = win_run(g, pi < np ? pi : 0);
+    const size_t pt = run.p;
     const int ne = g.nS, j0 = g.j0 - g.jA;
     const size_t sl = g.slice_e;
     // Stage P' and H' with batches of independent loads (clamped addresses,
@@ -975,8 +980,6 @@ __device__ __forceinline__ void e3_body(T *__restrict__ spec, const Geo &g)
                 const int it = it0 + k * kThreads;
                 const bool inP = it < nP;
                 const int row = inP ? it / TR : (it - nP) / TR;
-                const int p = it % TR;
-                const size_t pt = p0 + p;
                 int js;
                 bool ok;
                 if (inP) {
@@ -986,7 +989,7 @@ __device__ __forceinline__ void e3_body(T *__restrict__ spec, const Geo &g)
                     js = j0 + row - HP;
                     ok = row >= HP && js < ne;
                 }
-                ok = ok && it < nP + nH && pt < sl;
+                ok = ok && it < nP + nH && pi < np;
                 const size_t src = ok ? (size_t)js * sl + pt : 0;
                 const T x = spec[src];
                 v[k] = ok ? x : (T)0;
@@ -1060,11 +1063,15 @@ __device__ __forceinline__ void e3_body(T *__restrict__ spec, const Geo &g)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[i] += __shfl_xor(acc[i], o, 64);
         }
-        if (su == 0 && p0 + p < sl) {
+        if (su == 0 && pi < np) {
+            const long pm = win_mirror(g, run.t, run.r, (int)(pt & (g.Ce - 1)));
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const int m = mf + i;
-                if (m <= g.m_hi) spec[(size_t)(m - g.m_lo) * sl + p0 + p] = (T)acc[i];
+                if (m > g.m_hi) break;
+                T *dst = spec + (size_t)(m - g.m_lo) * sl;
+                dst[pt] = (T)acc[i];
+                if (pm >= 0) dst[pm] = (T)acc[i];
             }
         }
     }
@@ -1396,21 +1403,22 @@ __global__ void __launch_bounds__(kThreads, 4) k_e3m(T *__restrict__ spec, Geo g
     T *tile = overlay ? lds : lds + (size_t)TR * PS;
 
     if (prefetch) {
-        const E3mRsrc rs = e3m_rsrc(spec, sl, j0, nA, nHe, (size_t)t * TR);
+        const E3mRsrc rs = e3m_rsrc(spec, sl, j0, nA, nHe, win_run(g, (size_t)t * TR).p);
 #pragma unroll
         for (int k = 0; k < NPF; ++k) pf[k] = e3m_bload<T>(rs, st, r0 + k * RP);
 #pragma unroll
         for (int k = 0; k < NPF; ++k) e3m_put<T>(lds, PS, q * VEC, rows, r0 + k * RP, pf[k]);
     } else {
-        stage_sync((size_t)t * TR);
+        stage_sync(win_run(g, (size_t)t * TR).p);
     }
     __syncthreads();
     for (;;) {
-        const size_t p0 = (size_t)t * TR;
+        const WinRun run = win_run(g, (size_t)t * TR);
+        const size_t p0 = run.p;
         const int tn = t + bx;
         const bool more = tn < t_end;
         if (prefetch && more) {  // in flight during the products
-            const E3mRsrc rs = e3m_rsrc(spec, sl, j0, nA, nHe, (size_t)tn * TR);
+            const E3mRsrc rs = e3m_rsrc(spec, sl, j0, nA, nHe, win_run(g, (size_t)tn * TR).p);
             // The row offsets do not change from tile to tile; hiding r0 from
             // the optimiser keeps it from holding all NPF of them in registers
             // for the whole kernel (they are cheap to recompute).
@@ -1473,6 +1481,13 @@ __global__ void __launch_bounds__(kThreads, 4) k_e3m(T *__restrict__ spec, Geo g
                     for (int i = 0; i < VEC; ++i)
                         if (pb + i < sl) dst[i] = tile[row * TS + pq + i];
                 }
+                if (g.sw) {  // the exchanged points take the same values
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) {
+                        const long pm = win_mirror(g, run.t, run.r + ((pq + i) >> g.logCe), (pq + i) & (g.Ce - 1));
+                        if (pm >= 0) spec[(size_t)(m - g.m_lo) * sl + pm] = tile[row * TS + pq + i];
+                    }
+                }
             }
             __syncthreads();
         }
@@ -1482,7 +1497,7 @@ __global__ void __launch_bounds__(kThreads, 4) k_e3m(T *__restrict__ spec, Geo g
 #pragma unroll
             for (int k = 0; k < NPF; ++k) e3m_put<T>(lds, PS, q * VEC, rows, r0 + k * RP, pf[k]);
         } else
-            stage_sync((size_t)t * TR);
+            stage_sync(win_run(g, (size_t)t * TR).p);
         __syncthreads();
     }
 }
@@ -2999,7 +3014,7 @@ static hipError_t window_t(const Plan &pl, hipStream_t st)
         const size_t es = sizeof(T);
         const size_t lds3 = (size_t)(g.e3_PL + 16 * (64 >> g.e3_logTR) + 32 + g.m_lo + 16 * ((g.nL + 15) >> 4) - 1) *
                             g.e3_TR * es;
-        const dim3 g3(cdiv(g.slice_e, g.e3_TR));
+        const dim3 g3(cdiv(win_points(g), g.e3_TR));
 #define LH_E3(TRV)                                                                                    \
     do {                                                                                              \
         if (g.fp64)                                                                                   \
@@ -3014,7 +3029,7 @@ static hipError_t window_t(const Plan &pl, hipStream_t st)
         if (g.e3_variant == 1) {
             const size_t tile = (size_t)256 * (g.e3m_TR + 1), stage = (size_t)g.e3m_TR * g.e3m_PS;
             const size_t ldsm = (g.e3m_NMG == 1 ? std::max(tile, stage) : tile + stage) * es;
-            const int ntiles = (int)cdiv(g.slice_e, g.e3m_TR);
+            const int ntiles = (int)cdiv(win_points(g), g.e3m_TR);
             switch (g.e3m_TR) {
             case 32: return launch_e3m<T, 32>(pl, spr, ntiles, ldsm, st);
             case 16: return launch_e3m<T, 16>(pl, spr, ntiles, ldsm, st);
@@ -3057,7 +3072,7 @@ std::string even_group_key(const Plan &pl)
         g.e3_variant == 1)
         return std::string();
     char b[96];
-    std::snprintf(b, sizeof b, "e%d %d %d r%d w%d %d", g.fp64, g.logNx, g.logNy, pl.rho ? 1 : 0, g.e3_variant,
+    std::snprintf(b, sizeof b, "e%d %d %d r%d s%d w%d %d", g.fp64, g.logNx, g.logNy, pl.rho ? 1 : 0, g.sw, g.e3_variant,
                   g.e3_variant == 2 ? 16 : g.e3_TR);
     return b;
 }
@@ -3148,7 +3163,7 @@ static hipError_t even_group_t(const Plan *const *pls, int n, const EvenInst *d,
             return hipErrorInvalidValue;
         }
     } else {
-        const dim3 g3(cdiv(g.slice_e, g.e3_TR), 1, nz);
+        const dim3 g3(cdiv(win_points(g), g.e3_TR), 1, nz);
 #define LH_E3B(TRV)                                                                                                 \
     do {                                                                                                            \
         if (g.fp64)                                                                                                 \
