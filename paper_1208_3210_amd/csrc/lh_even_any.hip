@@ -16,8 +16,8 @@
 // energy window is the even path's.
 //
 // 2049^2 points x 512 energies x 256 lags with momentum density, FP32, against
-// the full complex Bluestein passes (ms): P1 16.7 -> 3.6, P2 11.1 -> 2.5, window
-// 7.3 -> 1.0, P4 5.7 -> 1.3, P5 9.7 -> 2.1; a call 50.4 -> 10.5.  300 x 257 x 128 x 64
+// the full complex Bluestein passes (ms): P1 16.7 -> 2.9, P2 11.1 -> 2.3, window
+// 7.3 -> 0.6, P4 5.7 -> 1.2, P5 9.7 -> 2.1; a call 50.6 -> 9.1.  300 x 257 x 128 x 64
 // in FP64: 0.66 -> 0.19.  Bound by the vector units (55 - 70 % busy) and the
 // latency of the exchanges at eighteen waves per CU.
 #include <algorithm>
@@ -53,11 +53,13 @@ constexpr int ev_threads()
 {
     return ev_lines<T, LOGM>() * EvenFFT<T, LOGM>::TL;
 }
-// Pairs of energies a block of the builder takes side by side.
+// Pairs of energies a block of the builder takes side by side: more of them share
+// the band values, fewer leave longer pieces of the 128-byte lines to a block
+// (2049^2 x 512: 3.07 ms with one, 2.89 with two, 3.56 with four).
 template <typename T, int LOGM>
 constexpr int ev_pairs()
 {
-    return ev_lines<T, LOGM>() < 4 ? ev_lines<T, LOGM>() : 4;
+    return 2;
 }
 // LDS values between lines: the row passes run consecutive lanes along one
 // line; the column passes interleave the lines lane by lane, so there the line
