@@ -411,7 +411,7 @@ lindhard_status plan_describe(const lindhard_problem *p, Plan &pl)
             if ((1 << ilog2(np)) > np) R = std::min(R, 1 << (ilog2(np) - 1));
             return std::max(1, R);
         };
-        g.e1_R = rows_per_block(e1_elems(g.logNx));
+        g.e1_R = rows_per_block(kE1Elems);
         g.e5_R = rows_per_block(16);
         if (!g.fp64 && g.logNx >= 10 && g.logNx <= 11) {
             // FP32 rows of 1024 and 2048 points (padded engine): kE5MaxThreads per block
@@ -556,8 +556,8 @@ std::vector<BufSpec> plan_buffers(const Plan &cpl)
         {&pl.bspec, band_ws ? (size_t)pl.nb * g.nS * sl : 0},
         {&pl.sacc, pair_ws ? (size_t)g.nL * sl : 0},
         {&pl.twx, g.nkx * cs},
-        {&pl.twy, g.nky * cs},
-        {&pl.twz, g.nkz * cs},
+        {&pl.twy, se_cols(g) ? 0 : g.nky * cs},
+        {&pl.twz, g.nkz > 1 ? g.nkz * cs : 0},
         {&pl.bsx[0], g.bs ? g.nkx * cs : 0},
         {&pl.bsy[0], g.bs ? g.nky * cs : 0},
         {&pl.bsx[1], bse ? even_any_spectrum_len(g.logMx) * cs : Mx},
@@ -566,7 +566,7 @@ std::vector<BufSpec> plan_buffers(const Plan &cpl)
         {&pl.bsy[1], bse ? even_any_spectrum_len(g.logMy) * cs : My},
         {&pl.bsy[2], bse ? even_any_twiddle_len(g.logMy) * cs : My},
         {&pl.bsy[3], bse ? 0 : My},
-        {&pl.twe, ((size_t)1 << g.logNE) * cs},
+        {&pl.twe, g.even ? 0 : ((size_t)1 << g.logNE) * cs},
         {(void **)&pl.ffx, (size_t)pl.out_nx * 16},
         {(void **)&pl.ffy, (size_t)pl.out_ny * 16},
         {(void **)&pl.d_src, nw * sizeof(PlaneSrc)},
@@ -579,6 +579,8 @@ std::vector<BufSpec> plan_buffers(const Plan &cpl)
         {(void **)&pl.kkw, rpa ? (size_t)pl.kk_ntiles * 16 * pl.kk_nch * 16 * 8 : 0},
         {(void **)&pl.d_kkrow, rpa ? pl.kk_rows.size() * sizeof(int2) : 0},
         {(void **)&pl.d_kkslot, rpa ? pl.kk_slot.size() * sizeof(int) : 0},
+        {&pl.evx, se_rows(g) ? even_any_twiddle_len(g.logNx) * cs : 0},
+        {&pl.evy, se_cols(g) ? even_any_twiddle_len(g.logNy) * cs : 0},
         {&pl.m2, pl.has_m2 ? (size_t)pl.nb * pl.nb * pl.out_nx * pl.out_ny * es : 0},
     };
 }
@@ -683,7 +685,7 @@ void plan_free(Plan &pl)
                      &pl.im1,             &pl.re1,           (void **)&pl.kkw, (void **)&pl.scratch,
                      &pl.rho,              &pl.bspec,         &pl.sacc,         &pl.bsx[0], &pl.bsx[1], &pl.bsx[2], &pl.bsx[3],
                      &pl.bsy[0],           &pl.bsy[1],        &pl.bsy[2], &pl.bsy[3], (void **)&pl.d_kkrow,
-                     (void **)&pl.d_kkslot, &pl.m2};
+                     (void **)&pl.d_kkslot, &pl.m2, &pl.evx, &pl.evy};
     for (void **p : ptrs) *p = nullptr;
 }
 
@@ -1046,6 +1048,18 @@ static hipError_t put_table(const Plan &pl, const std::vector<std::complex<doubl
     return hipMemcpyAsync(dst, hd, nv * (pl.g.fp64 ? sizeof(double) : sizeof(float)), hipMemcpyHostToDevice, st);
 }
 
+// EvenFFT twiddles of a power-of-two axis.
+static hipError_t even_tables(const Plan &pl, int logN, void *dst, hipStream_t st, std::vector<std::vector<double>> &keep)
+{
+    std::vector<std::complex<double>> t(even_any_twiddle_len(logN));
+    const size_t N = (size_t)1 << logN;
+    for (size_t e = 0; e < t.size(); ++e) {
+        const double ang = -2.0 * M_PI * (double)(even_any_twiddle_index(logN, e) & (N - 1)) / (double)N;
+        t[e] = std::complex<double>(std::cos(ang), std::sin(ang));
+    }
+    return put_table(pl, t, 1.0, dst, st, keep);
+}
+
 // Bluestein tables of one axis of length n (a grid of any size): chirp
 // b_k = exp(i pi (k^2 mod 2n) / n), the spectra FFT_M(B) / M and FFT_M(conj B) / M
 // of the chirp sequence B (B_m = b_m = B_(M-m) for m < n, zero between; with
@@ -1196,6 +1210,8 @@ static lindhard_status build_plan_object(const lindhard_problem *p, lindhard_pla
         LH_TRY(bs_tables(pl, pl.g.nkx, pl.g.logMx, pl.bsx, st, keep));
         LH_TRY(bs_tables(pl, pl.g.nky, pl.g.logMy, pl.bsy, st, keep));
     }
+    if (pl.evx) LH_TRY(even_tables(pl, pl.g.logNx, pl.evx, st, keep));
+    if (pl.evy) LH_TRY(even_tables(pl, pl.g.logNy, pl.evy, st, keep));
     const size_t nk = (size_t)pl.g.nkx * pl.g.nky * pl.g.nkz;
     if (pl.p.want_rpa)
         LH_TRY(hipMemsetAsync(pl.im1, 0, (size_t)pl.g.neps * nk * pl.elem_bytes, st));

@@ -98,8 +98,6 @@ struct Geo {
 // Elements per thread of the register FFTs in the even builder pass (the
 // builder also keeps the band rows of its lines in registers).
 constexpr int kE1Elems = 8;
-// ... except on 4096-point rows, where eight would take 512 threads per line
-constexpr int e1_elems(int logn) { return logn >= 12 ? 16 : kE1Elems; }
 // Threads per block of the last even row pass: up to 512 (FP32 rows of 1024
 // and 2048 points take four lines per block: with the padded engine the
 // block's lines and twiddle table fit twice per CU, sixteen waves against the
@@ -135,6 +133,7 @@ struct Plan {
     void *twx = nullptr;       // cx<T>[nkx]
     void *twy = nullptr;       // cx<T>[nky]
     void *twz = nullptr;       // cx<T>[nkz] (three dimensions)
+    void *evx = nullptr, *evy = nullptr;  // EvenFFT twiddles of the axes (se_rows, se_cols)
     // grids of any size: per axis chirp b, chirp spectra hf / hi, FFT twiddles of length M
     // (even path: chirp, spectrum and twiddles in EvenFFT's order)
     void *bsx[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -184,7 +183,7 @@ struct Plan {
 struct EvenInst {
     Geo g;
     const double *xi;
-    const void *rho, *twx, *twy;
+    const void *rho, *twx, *twy, *evx, *evy;
     void *spec;
     const PlaneSrc *psrc;
     void *out;
@@ -237,6 +236,14 @@ size_t even_any_spectrum_len(int logM);
 size_t even_any_spectrum_index(int logM, size_t e);
 size_t even_any_twiddle_len(int logM);
 size_t even_any_twiddle_index(int logM, size_t e);
+// The even path's passes on EvenFFT (lh_even_pow2.hip): P1 of one band, P2 / P4
+// over n slices, and the rules that choose them (the sizes from which they
+// measured faster).
+inline bool se_rows(const Geo &g) { return g.even && !g.bs && g.logNx >= 10; }
+inline bool se_cols(const Geo &g) { return g.even && !g.bs && g.logNy >= (g.fp64 ? 9 : 10); }
+hipError_t launch_se_group(const Plan *const *pls, int n, const EvenInst *d_desc, int pass, hipStream_t st);
+hipError_t launch_se1(const Plan &pl, void *spec, int band, int acc, hipStream_t st);
+hipError_t launch_secol(const Plan &pl, void *spec, int n, bool inv, hipStream_t st);
 hipError_t launch_cut(const Plan &pl, const void *im, const int *xy, int npts, void *out, hipStream_t st);
 // res: 3 + 4 * nseg doubles of device memory; im_plane: the plane to cut
 hipError_t launch_envelope(const Plan &pl, const void *im_plane, int dir, int W, int nseg, double qstep, double *res,

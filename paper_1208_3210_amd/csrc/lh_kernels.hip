@@ -742,7 +742,7 @@ __device__ __forceinline__ void e1_body(const double *__restrict__ xi, const Geo
                                                 double gamma, const cx<T> *__restrict__ twx, T *__restrict__ spec,
                                                 const T *__restrict__ rho, int acc)
 {
-    constexpr int LOGE = ilog2_c(e1_elems(LOGNX));
+    constexpr int LOGE = ilog2_c(kE1Elems);
     using F = RegFFT<T, LOGNX, false, LOGE, kTwLds<T>>;
     using FP = RegFFTP<T, LOGNX, false, LOGE, kRowPB>;
     constexpr bool PADDED = row_padded<T, LOGNX, LOGE>();
@@ -864,7 +864,7 @@ __device__ __forceinline__ void e1_body(const double *__restrict__ xi, const Geo
 }
 
 template <typename T, int LOGNX, bool W>
-__global__ void __launch_bounds__(kThreads, (sizeof(T) == 4 && LOGNX < 12) ? 4 : 1) k_e1(const double *__restrict__ xi, Geo g, double emin, double deps,
+__global__ void __launch_bounds__(kThreads, sizeof(T) == 4 ? 4 : 1) k_e1(const double *__restrict__ xi, Geo g, double emin, double deps,
                                                 double gamma, const cx<T> *__restrict__ twx, T *__restrict__ spec,
                                                 const T *__restrict__ rho, int acc)
 {
@@ -872,7 +872,7 @@ __global__ void __launch_bounds__(kThreads, (sizeof(T) == 4 && LOGNX < 12) ? 4 :
 }
 // Batched P1: instance blockIdx.z of the descriptors (band 0, no accumulation)
 template <typename T, int LOGNX, bool W>
-__global__ void __launch_bounds__(kThreads, (sizeof(T) == 4 && LOGNX < 12) ? 4 : 1) k_e1_batch(const EvenInst *__restrict__ in)
+__global__ void __launch_bounds__(kThreads, sizeof(T) == 4 ? 4 : 1) k_e1_batch(const EvenInst *__restrict__ in)
 {
     const EvenInst &d = in[blockIdx.z];
     const Geo g = d.g;
@@ -2469,11 +2469,11 @@ template <typename T>
 static hipError_t tables_t(const Plan &pl, hipStream_t st)
 {
     const Geo &g = pl.g;
-    hipLaunchKernelGGL(k_twiddle<T>, dim3(cdiv(g.nkx, kThreads)), dim3(kThreads), 0, st, (cx<T> *)pl.twx, g.nkx);
-    hipLaunchKernelGGL(k_twiddle<T>, dim3(cdiv(g.nky, kThreads)), dim3(kThreads), 0, st, (cx<T> *)pl.twy, g.nky);
-    hipLaunchKernelGGL(k_twiddle<T>, dim3(cdiv(g.nkz, kThreads)), dim3(kThreads), 0, st, (cx<T> *)pl.twz, g.nkz);
-    hipLaunchKernelGGL(k_twiddle<T>, dim3(cdiv(1 << g.logNE, kThreads)), dim3(kThreads), 0, st, (cx<T> *)pl.twe,
-                       1 << g.logNE);
+    const std::pair<void *, int> tw[] = {{pl.twx, g.nkx}, {pl.twy, g.nky}, {pl.twz, g.nkz}, {pl.twe, 1 << g.logNE}};
+    for (const auto &t : tw)  // (a plan holds the tables its passes read)
+        if (t.first)
+            hipLaunchKernelGGL(k_twiddle<T>, dim3(cdiv(t.second, kThreads)), dim3(kThreads), 0, st, (cx<T> *)t.first,
+                               t.second);
     if (pl.p.ff_kind != LINDHARD_FF_NONE) {
         hipLaunchKernelGGL(k_fftab, dim3(cdiv(pl.out_nx, kThreads)), dim3(kThreads), 0, st, pl.ffx, g.nkx, pl.zx,
                            pl.ff_s, pl.p.k_zones);
@@ -2566,10 +2566,10 @@ template <typename T, int LOGNX>
 static void launch_e1(const Plan &pl, T *spec, int band, int acc, hipStream_t st)
 {
     const Geo &g = pl.g;
-    using F = RegFFT<T, LOGNX, false, ilog2_c(e1_elems(LOGNX))>;
+    using F = RegFFT<T, LOGNX, false, ilog2_c(kE1Elems)>;
     const int np = (g.Hy + 1) / 2;
     const dim3 grid(cdiv(np, g.e1_R), cdiv(g.nS, g.e1_jc));
-    const size_t lds = row_lds_bytes<T, LOGNX, ilog2_c(e1_elems(LOGNX))>(g.e1_R);
+    const size_t lds = row_lds_bytes<T, LOGNX, ilog2_c(kE1Elems)>(g.e1_R);
     const size_t nk = (size_t)g.nkx * g.nky;
     const double *xi = pl.xi + band * nk;
     if (pl.rho)
@@ -2606,6 +2606,20 @@ static void launch_e5(const Plan &pl, const T *spec, int nplanes, T *out, int on
                        (const cx<T> *)pl.twx, pl.d_src, pl.scale, pl.zx, pl.zy, ff, pl.ff_s, pl.ffx, pl.ffy, out,
                        onx, ony, m2, acc);
 }
+
+// Up to 512 points (the even builder and columns; longer axes: se_rows, se_cols)
+#define LH_SWITCH_LOG9(v, CALL)                  \
+    switch (v) {                                 \
+    case 2: CALL(2); break;                      \
+    case 3: CALL(3); break;                      \
+    case 4: CALL(4); break;                      \
+    case 5: CALL(5); break;                      \
+    case 6: CALL(6); break;                      \
+    case 7: CALL(7); break;                      \
+    case 8: CALL(8); break;                      \
+    case 9: CALL(9); break;                      \
+    default: return hipErrorInvalidValue;        \
+    }
 
 #define LH_SWITCH_LOG(v, CALL)                   \
     switch (v) {                                 \
@@ -2798,9 +2812,10 @@ static hipError_t exec_t(const Plan &pl, T *out, hipStream_t st, hipEvent_t *ev)
     const size_t sb = g.even ? g.slice_e * sizeof(T) : g.slice_elems * sizeof(cx<T>);  // bytes per slice
     // P1 of one band into dst (acc: added to what dst holds)
     auto p1 = [&](void *dst, int band, int acc) -> hipError_t {
+        if (se_rows(g)) return launch_se1(pl, dst, band, acc, st);
         if (g.even) {
 #define LH_E1(LG) launch_e1<T, LG>(pl, (T *)dst, band, acc, st)
-            LH_SWITCH_LOG12(g.logNx, LH_E1)
+            LH_SWITCH_LOG9(g.logNx, LH_E1)
 #undef LH_E1
         } else {
             for (int z = 0; z < g.nkz; ++z) {
@@ -2814,14 +2829,15 @@ static hipError_t exec_t(const Plan &pl, T *out, hipStream_t st, hipEvent_t *ev)
     };
     // forward (P2) or inverse (P4) column pass over n slices of buf
     auto col = [&](void *buf, int n, bool inv) -> hipError_t {
+        if (se_cols(g)) return launch_secol(pl, buf, n, inv, st);
         if (g.even) {
             if (inv) {
 #define LH_E4(LG) launch_ecol<T, LG, true>(pl, (T *)buf, n, st)
-                LH_SWITCH_LOG12(g.logNy, LH_E4)
+                LH_SWITCH_LOG9(g.logNy, LH_E4)
 #undef LH_E4
             } else {
 #define LH_E2(LG) launch_ecol<T, LG, false>(pl, (T *)buf, n, st)
-                LH_SWITCH_LOG12(g.logNy, LH_E2)
+                LH_SWITCH_LOG9(g.logNy, LH_E2)
 #undef LH_E2
             }
         } else {
@@ -3084,6 +3100,8 @@ void even_group_fill(const Plan &pl, void *out, EvenInst &d)
     d.rho = pl.rho;
     d.twx = pl.twx;
     d.twy = pl.twy;
+    d.evx = pl.evx;
+    d.evy = pl.evy;
     d.spec = pl.spec;
     d.psrc = pl.d_src;
     d.out = out;
@@ -3126,15 +3144,19 @@ static hipError_t even_group_t(const Plan *const *pls, int n, const EvenInst *d,
     // P1
 #define LH_E1B(LG)                                                                                                  \
     do {                                                                                                            \
-        using F = RegFFT<T, LG, false, ilog2_c(e1_elems(LG))>;                                                     \
-        const size_t lds = row_lds_bytes<T, LG, ilog2_c(e1_elems(LG))>(g.e1_R);                                    \
+        using F = RegFFT<T, LG, false, ilog2_c(kE1Elems)>;                                                     \
+        const size_t lds = row_lds_bytes<T, LG, ilog2_c(kE1Elems)>(g.e1_R);                                    \
         const dim3 grid(cdiv(np, g.e1_R), ys1, nz);                                                                 \
         if (rho)                                                                                                    \
             hipLaunchKernelGGL((k_e1_batch<T, LG, true>), grid, dim3(g.e1_R * F::G), lds, st, d);                   \
         else                                                                                                        \
             hipLaunchKernelGGL((k_e1_batch<T, LG, false>), grid, dim3(g.e1_R * F::G), lds, st, d);                  \
     } while (0)
-    LH_SWITCH_LOG12(g.logNx, LH_E1B)
+    if (se_rows(g)) {
+        LH_HIP_TRY(launch_se_group(pls, n, d, 1, st));
+    } else {
+        LH_SWITCH_LOG9(g.logNx, LH_E1B)
+    }
 #undef LH_E1B
     // P2 / P4
     auto col = [&](int ns, bool inv) -> hipError_t {
@@ -3150,7 +3172,8 @@ static hipError_t even_group_t(const Plan *const *pls, int n, const EvenInst *d,
         else                                                                                                        \
             hipLaunchKernelGGL((k_ecol_batch<T, LG, false>), grid, dim3(F::G * TPB * C), lds, st, d);               \
     } while (0)
-        LH_SWITCH_LOG12(g.logNy, LH_ECB)
+        if (se_cols(g)) return launch_se_group(pls, n, d, inv ? 4 : 2, st);
+        LH_SWITCH_LOG9(g.logNy, LH_ECB)
 #undef LH_ECB
         return hipGetLastError();
     };
