@@ -2,6 +2,7 @@
 #pragma once
 #include "lh_fft.h"
 #include "lh_internal.h"
+#include "lh_regfft.h"
 
 namespace lh {
 
@@ -86,6 +87,41 @@ __device__ __forceinline__ long win_mirror(const Geo &g, int t, int r, int c)
     const int rx = t * g.Ce + c, t2 = r >> g.logCe;
     if (!g.sw || t2 <= t || rx > g.L || r >= g.Hy) return -1;
     return ((long)t2 * g.HyS + rx) * g.Ce + (r & (g.Ce - 1));
+}
+
+// FP32: an FFT twiddle table of n values copied into LDS at dst (stored with
+// tw_swz), so that the transform passes read it there rather than waiting on
+// the cache for every pass; returns the table to use.  FP64 keeps the global table (it would
+// double the LDS of the blocks that use it).  Every thread of the block calls
+// it (it ends with a barrier when it copies).
+template <typename T>
+constexpr bool kTwLds = sizeof(T) == 4;  // the kernels that copy their twiddles into LDS (FP32)
+template <typename T>
+__device__ __forceinline__ const cx<T> *tw_to_lds(const cx<T> *tw, cx<T> *dst, int n, int tid, int nthr)
+{
+    if constexpr (kTwLds<T>) {
+        for (int i = tid; i < n; i += nthr) dst[tw_swz(i)] = tw[i];  // the layout RegFFT<..., true> reads
+        __syncthreads();
+        return dst;
+    } else {
+        return tw;
+    }
+}
+// LDS bytes of such a table
+template <typename T>
+constexpr size_t tw_lds_bytes(int n)
+{
+    return sizeof(T) == 4 ? (size_t)n * sizeof(cx<T>) : 0;
+}
+
+// Blocks are dispatched round-robin over the 8 XCDs (each with its own L2).
+// Map launch index b to a logical tile so that consecutive logical tiles run
+// on the same XCD: tiles sharing cache lines then meet in the same L2.
+__device__ __forceinline__ unsigned xcd_tile(unsigned b, unsigned nblocks)
+{
+    const unsigned per = nblocks >> 3;          // full rounds of 8
+    if (b >= (per << 3)) return b;              // ragged tail keeps its index
+    return (b & 7) * per + (b >> 3);
 }
 
 // LDS written by some lanes of a wave is read by others of the same wave: the

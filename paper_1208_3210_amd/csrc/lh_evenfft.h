@@ -33,54 +33,6 @@
 
 namespace lh {
 
-// rdft of R points whose inputs outside the bit mask NZ are zero (they are not
-// read); natural order in and out.
-template <typename T, int R, bool INV, unsigned NZ>
-__device__ __forceinline__ void rdft_nz(cx<T> *v)
-{
-    static_assert(NZ != 0, "some input is not zero");
-    if constexpr (R == 2) {
-        const cx<T> a = v[0], b = v[1];
-        if constexpr (NZ == 3u) {
-            v[0] = cadd(a, b);
-            v[1] = csub(a, b);
-        } else if constexpr (NZ == 1u) {
-            v[1] = a;
-        } else {
-            v[0] = b;
-            v[1] = mk<T>(-b.x, -b.y);
-        }
-    } else if constexpr (R > 2) {
-        constexpr unsigned half = [] {
-            unsigned e = 0, o = 0;
-            for (int i = 0; i < R / 2; ++i) {
-                e |= ((NZ >> (2 * i)) & 1u) << i;
-                o |= ((NZ >> (2 * i + 1)) & 1u) << i;
-            }
-            return e | (o << 16);
-        }();
-        constexpr unsigned NE = half & 0xFFFFu, NO = half >> 16;
-        cx<T> e[R / 2], o[R / 2];
-#pragma unroll
-        for (int i = 0; i < R / 2; ++i) {
-            e[i] = v[2 * i];
-            o[i] = v[2 * i + 1];
-        }
-        if constexpr (NE != 0) rdft_nz<T, R / 2, INV, NE>(e);
-        if constexpr (NO != 0) rdft_nz<T, R / 2, INV, NO>(o);
-        if constexpr (NE != 0 && NO != 0) {
-            rdft_combine<T, R, INV>(v, e, o);
-        } else if constexpr (NE != 0) {
-#pragma unroll
-            for (int i = 0; i < R / 2; ++i) v[i] = v[i + R / 2] = e[i];
-        } else {
-            const cx<T> z = mk<T>((T)0, (T)0);
-            for (int i = 0; i < R / 2; ++i) e[i] = z;
-            rdft_combine<T, R, INV>(v, e, o);
-        }
-    }
-}
-
 template <typename T, int LOGN>
 struct EvenFFT {
     static_assert(LOGN >= 8 && LOGN <= 12, "256 to 4096 points");

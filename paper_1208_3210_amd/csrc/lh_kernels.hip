@@ -151,41 +151,6 @@ __global__ void __launch_bounds__(kThreads) k_kkw(double *__restrict__ w, const 
     w[idx] = (lag >= 0 && j < neps) ? kk_weight(lag, j) : 0.0;
 }
 
-// Blocks are dispatched round-robin over the 8 XCDs (each with its own L2).
-// Map launch index b to a logical tile so that consecutive logical tiles run
-// on the same XCD: tiles sharing cache lines then meet in the same L2.
-__device__ __forceinline__ unsigned xcd_tile(unsigned b, unsigned nblocks)
-{
-    const unsigned per = nblocks >> 3;          // full rounds of 8
-    if (b >= (per << 3)) return b;              // ragged tail keeps its index
-    return (b & 7) * per + (b >> 3);
-}
-
-// FP32: an FFT twiddle table of n values copied into LDS at dst (stored with
-// tw_swz), so that the transform passes read it there rather than waiting on
-// the cache for every pass; returns the table to use.  FP64 keeps the global table (it would
-// double the LDS of the blocks that use it).  Every thread of the block calls
-// it (it ends with a barrier when it copies).
-template <typename T>
-constexpr bool kTwLds = sizeof(T) == 4;  // the kernels that copy their twiddles into LDS (FP32)
-template <typename T>
-__device__ __forceinline__ const cx<T> *tw_to_lds(const cx<T> *tw, cx<T> *dst, int n, int tid, int nthr)
-{
-    if constexpr (kTwLds<T>) {
-        for (int i = tid; i < n; i += nthr) dst[tw_swz(i)] = tw[i];  // the layout RegFFT<..., true> reads
-        __syncthreads();
-        return dst;
-    } else {
-        return tw;
-    }
-}
-// LDS bytes of such a table
-template <typename T>
-constexpr size_t tw_lds_bytes(int n)
-{
-    return sizeof(T) == 4 ? (size_t)n * sizeof(cx<T>) : 0;
-}
-
 // Row passes (the even path's builder and both paths' last row passes)
 // in FP32 use the padded-layout engine (padding period 32) when a line spans
 // whole waves (at least 64 threads); FP64 keeps its twiddles in global memory
@@ -501,73 +466,6 @@ __global__ void __launch_bounds__(kThreads) k_p3(cx<T> *__restrict__ spec, Geo g
                         COMP ? mk<T>(hi[i].x + lo[i].x, hi[i].y + lo[i].y) : hi[i];
             }
         }
-    }
-}
-
-// Energy-window product by FFT along the energy axis.  For one real-space
-// point let P_j = B(r, j) for occupied j and H_j = B(r, j) for unoccupied j
-// (zero elsewhere).  Because every occupied index lies below every unoccupied
-// one, the circular correlation of length N >= (number of slices) equals the
-// linear one for 0 <= m < N, so
-//   S(r, m) = sum_j conj(P_j) H_{j+m} = IFFT_N( conj(FFT_N P) * FFT_N H )(m) / N.
-// One block: TR real-space points (RY rows of one column tile), G threads per
-// point; the slices are staged through LDS, which is then reused as the FFT
-// line buffers.  Written in place over the slices, as the direct form.
-template <typename T, int LOGN>
-__global__ void __launch_bounds__(512) k_p3f(cx<T> *__restrict__ spec, Geo g, const cx<T> *__restrict__ twe)
-{
-    using FF = RegFFT<T, LOGN, false, 4, kTwLds<T>>;
-    using FI = RegFFT<T, LOGN, true, 4, kTwLds<T>>;
-    constexpr int N = FF::N, E = FF::E, G = FF::G;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    cx<T> *lds = reinterpret_cast<cx<T> *>(smem_raw);  // [N][TR], then [TR][N]
-    const int TR = g.p3f_TR, logTR = g.p3f_logTR;
-    const int tid = threadIdx.x;
-    const int rp = tid & (TR - 1), gg = tid >> logTR;
-    const size_t off = ((size_t)blockIdx.x * g.nky + (size_t)blockIdx.y * (TR >> g.logC)) << g.logC;
-    const int ne = g.nS;
-    const int j0 = g.j0 - g.jA;
-    const int nthr = TR * G;
-    const cx<T> *tw = tw_to_lds<T>(twe, lds + TR * N, N, tid, nthr);
-    for (int it0 = tid; it0 < (ne << logTR); it0 += 8 * nthr) {
-        cx<T> v[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int it = it0 + k * nthr;
-            const int sl = it >> logTR, p = it & (TR - 1);
-            v[k] = spec[it < (ne << logTR) ? (size_t)sl * g.slice_elems + off + p : 0];
-        }
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-            if (it0 + k * nthr < (ne << logTR)) lds[it0 + k * nthr] = v[k];
-    }
-    __syncthreads();
-    const cx<T> zero = mk<T>((T)0, (T)0);
-    cx<T> vp[E], vh[E];
-#pragma unroll
-    for (int s = 0; s < E; ++s) {
-        const int j = gg + s * G;
-        const cx<T> b = j < ne ? lds[(j << logTR) + rp] : zero;
-        vp[s] = j < j0 ? b : zero;
-        vh[s] = j >= j0 ? b : zero;
-    }
-    __syncthreads();
-    cx<T> *buf = lds + rp * N;
-    const int lxe = lds_xor_interleaved<T, N>(rp, TR);
-    FF::run(vp, buf, tw, 0, gg, lxe);
-    FF::run(vh, buf, tw, 0, gg, lxe);
-#pragma unroll
-    for (int s = 0; s < E; ++s) {
-        const cx<T> a = vp[s], b = vh[s];
-        vh[s] = mk<T>(a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x);  // conj(a) b
-    }
-    FI::run(vh, buf, tw, 0, gg, lxe);
-    const T inv = (T)(1.0 / N);
-#pragma unroll
-    for (int s = 0; s < E; ++s) {
-        const int m = gg + s * G;
-        if (m >= g.m_lo && m <= g.m_hi)
-            spec[(size_t)(m - g.m_lo) * g.slice_elems + off + rp] = cscale(vh[s], inv);
     }
 }
 
@@ -2536,16 +2434,6 @@ static void launch_zcol(const Plan &pl, cx<T> *spec, int nslices, hipStream_t st
                        (const cx<T> *)pl.twz);
 }
 
-template <typename T, int LOGN>
-static void launch_p3f(const Plan &pl, cx<T> *spec, hipStream_t st)
-{
-    const Geo &g = pl.g;
-    using F = RegFFT<T, LOGN, false>;
-    hipLaunchKernelGGL((k_p3f<T, LOGN>), dim3(g.NT * g.nkz, g.nky / (g.p3f_TR >> g.logC)), dim3(g.p3f_TR * F::G),
-                       (size_t)g.p3f_TR * F::N * sizeof(cx<T>) + tw_lds_bytes<T>(F::N), st, spec, g,
-                       (const cx<T> *)pl.twe);
-}
-
 template <typename T, int LOGL, int MODE>
 static void launch_p5(const Plan &pl, const cx<T> *spec, int nplanes, T *out, int onx, int ony, hipStream_t st,
                       const T *m2 = nullptr, int acc = 0)
@@ -3067,9 +2955,7 @@ static hipError_t window_t(const Plan &pl, hipStream_t st)
     }
     cx<T> *spec = (cx<T> *)pl.spec;
     if (g.p3_variant == 1) {
-#define LH_P3F(LG) launch_p3f<T, LG>(pl, spec, st)
-        LH_SWITCH_LOG(g.logNE, LH_P3F)
-#undef LH_P3F
+        return launch_p3f(pl, st);
     } else if (g.fp64) {
         hipLaunchKernelGGL((k_p3<T, false>), dim3(g.NT * g.nkz, g.nky / g.p3_RY), dim3(kThreads), (size_t)g.nS * g.p3_TR * cs,
                            st, spec, g);

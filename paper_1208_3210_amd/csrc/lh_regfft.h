@@ -96,6 +96,54 @@ __device__ __forceinline__ void rdft(cx<T> *v)
     }
 }
 
+// rdft of R points whose inputs outside the bit mask NZ are zero (they are not
+// read); natural order in and out.
+template <typename T, int R, bool INV, unsigned NZ>
+__device__ __forceinline__ void rdft_nz(cx<T> *v)
+{
+    static_assert(NZ != 0, "some input is not zero");
+    if constexpr (R == 2) {
+        const cx<T> a = v[0], b = v[1];
+        if constexpr (NZ == 3u) {
+            v[0] = cadd(a, b);
+            v[1] = csub(a, b);
+        } else if constexpr (NZ == 1u) {
+            v[1] = a;
+        } else {
+            v[0] = b;
+            v[1] = mk<T>(-b.x, -b.y);
+        }
+    } else if constexpr (R > 2) {
+        constexpr unsigned half = [] {
+            unsigned e = 0, o = 0;
+            for (int i = 0; i < R / 2; ++i) {
+                e |= ((NZ >> (2 * i)) & 1u) << i;
+                o |= ((NZ >> (2 * i + 1)) & 1u) << i;
+            }
+            return e | (o << 16);
+        }();
+        constexpr unsigned NE = half & 0xFFFFu, NO = half >> 16;
+        cx<T> e[R / 2], o[R / 2];
+#pragma unroll
+        for (int i = 0; i < R / 2; ++i) {
+            e[i] = v[2 * i];
+            o[i] = v[2 * i + 1];
+        }
+        if constexpr (NE != 0) rdft_nz<T, R / 2, INV, NE>(e);
+        if constexpr (NO != 0) rdft_nz<T, R / 2, INV, NO>(o);
+        if constexpr (NE != 0 && NO != 0) {
+            rdft_combine<T, R, INV>(v, e, o);
+        } else if constexpr (NE != 0) {
+#pragma unroll
+            for (int i = 0; i < R / 2; ++i) v[i] = v[i + R / 2] = e[i];
+        } else {
+            const cx<T> z = mk<T>((T)0, (T)0);
+            for (int i = 0; i < R / 2; ++i) e[i] = z;
+            rdft_combine<T, R, INV>(v, e, o);
+        }
+    }
+}
+
 __device__ __forceinline__ int swz(int x) { return x ^ ((x >> 4) & 15); }
 
 // Twiddle tables kept in LDS are stored with this XOR swizzle (a bijection on
@@ -103,8 +151,9 @@ __device__ __forceinline__ int swz(int x) { return x ^ ((x >> 4) & 15); }
 // butterflies of a wave, otherwise fall into a few LDS banks.
 __host__ __device__ constexpr int tw_swz(int i) { return i ^ ((i >> 5) & 31); }
 
-// TWS: the twiddle table is stored with tw_swz.
-template <typename T, int LOGN, bool INV, int LOGE_MAX = 4, bool TWS = false>
+// TWS: the twiddle table is stored with tw_swz.  NZ: the inputs v[s] that may not
+// be zero (bit s; the others are not read).
+template <typename T, int LOGN, bool INV, int LOGE_MAX = 4, bool TWS = false, unsigned NZ = 0xFFFFFFFFu>
 struct RegFFT {
     static constexpr int N = 1 << LOGN;
     static constexpr int LOGE = LOGN < LOGE_MAX ? LOGN : LOGE_MAX;
@@ -150,7 +199,10 @@ struct RegFFT {
                     w[u * r + s] = cmul(w[u * r + s], twid<T, INV>(tw, TWS ? tw_swz(x) : x));
                 }
             }
-            rdft<T, r, INV>(w + u * r);
+            if constexpr (first && q == 1 && NZ != 0xFFFFFFFFu)
+                rdft_nz<T, r, INV, NZ>(w);
+            else
+                rdft<T, r, INV>(w + u * r);
             if constexpr (last) {
 #pragma unroll
                 for (int s = 0; s < r; ++s) v[u + s * q] = w[u * r + s];
@@ -245,7 +297,8 @@ __device__ __forceinline__ cx<T> rot16(cx<T> a, int m)
     return INV ? mk<T>(a.x * c - a.y * s, a.y * c + a.x * s) : mk<T>(a.x * c + a.y * s, a.y * c - a.x * s);
 }
 
-template <typename T, int LOGN, bool INV, int LOGE_MAX, int PB>
+// NZ: the inputs v[s] that may not be zero (bit s; the others are not read).
+template <typename T, int LOGN, bool INV, int LOGE_MAX, int PB, unsigned NZ = 0xFFFFFFFFu>
 struct RegFFTP {
     static constexpr int N = 1 << LOGN;
     static constexpr int LOGE = LOGN < LOGE_MAX ? LOGN : LOGE_MAX;
@@ -329,7 +382,10 @@ struct RegFFTP {
                     w[u * r + s] = cmul(w[u * r + s], tws);
                 }
             }
-            rdft<T, r, INV>(w + u * r);
+            if constexpr (first && q == 1 && NZ != 0xFFFFFFFFu)
+                rdft_nz<T, r, INV, NZ>(w);
+            else
+                rdft<T, r, INV>(w + u * r);
             if constexpr (last) {
 #pragma unroll
                 for (int s = 0; s < r; ++s) v[u + s * q] = w[u * r + s];
