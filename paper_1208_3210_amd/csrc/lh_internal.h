@@ -229,6 +229,9 @@ hipError_t launch_window(const Plan &pl, hipStream_t st);  // energy-window pass
 // The even window as 4 x 4 rank-1 matrix updates (FP32), W waves per block.
 size_t e3q_lds_bytes(const Geo &g, int W);
 hipError_t launch_e3q(const Plan &pl, int W, hipStream_t st);
+// The same for band pairs, reading the bands' spectra (bspec) in place.
+bool e3q_mix_ok(const Plan &pl);
+hipError_t launch_e3q_mix(const Plan &pl, int nu, const double *w, void *out, bool acc, hipStream_t st);
 // The mirror-symmetric path on grids of any size: pass 1, 2, 4 or 5, and the
 // order of its per-axis tables.
 hipError_t launch_even_any(const Plan &pl, int pass, void *out, hipStream_t st);

@@ -15,6 +15,7 @@
 #include "lh_device.h"
 #include "lh_regfft.h"
 
+#include <algorithm>
 #include <map>
 #include <mutex>
 
@@ -2818,6 +2819,14 @@ static hipError_t exec_t(const Plan &pl, T *out, hipStream_t st, hipEvent_t *ev)
         const size_t nemp = (size_t)g.nS - nocc;
         for (size_t k = 0; k < pl.m2_pairs.size(); ++k) {
             const size_t nu = (size_t)pl.m2_pairs[k] / nb, mu = (size_t)pl.m2_pairs[k] % nb;
+            if (e3q_mix_ok(pl)) {
+                double one[LINDHARD_MAX_BANDS] = {};
+                one[mu] = 1.0;
+                LH_HIP_TRY(launch_e3q_mix(pl, (int)nu, one, pl.spec, false, st));
+                LH_HIP_TRY(col(pl.spec, g.nL, true));
+                LH_HIP_TRY(p5(pl.spec, (const T *)pl.m2 + (size_t)pl.m2_pairs[k] * plane_out, k > 0));
+                continue;
+            }
             if (nocc > 0) LH_HIP_TRY(hipMemcpyAsync(sp, bs + nu * g.nS * sb, nocc * sb, hipMemcpyDeviceToDevice, st));
             if (nemp > 0)
                 LH_HIP_TRY(hipMemcpyAsync(sp + nocc * sb, bs + (mu * g.nS + nocc) * sb, nemp * sb,
@@ -2847,6 +2856,12 @@ static hipError_t exec_t(const Plan &pl, T *out, hipStream_t st, hipEvent_t *ev)
         const size_t nemp = (size_t)g.nS - nocc;
         int done = 0;
         for (size_t nu = 0; nu < nb; ++nu) {
+            if (e3q_mix_ok(pl)) {
+                const double *w = &pl.pairw[nu * nb];
+                if (std::all_of(w, w + nb, [](double x) { return x == 0.0; })) continue;
+                LH_HIP_TRY(launch_e3q_mix(pl, (int)nu, w, pl.sacc, done++ > 0, st));
+                continue;
+            }
             int terms = 0;
             for (size_t mu = 0; mu < nb; ++mu) {
                 const double w = pl.pairw[nu * nb + mu];
