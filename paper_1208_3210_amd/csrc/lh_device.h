@@ -23,12 +23,14 @@ __device__ __forceinline__ float lorentz(float d, float gp, float g2)
 }
 __device__ __forceinline__ double lorentz(double d, double gp, double g2) { return gp / (d * d + g2); }
 
-// |M(Q)|^2 = F(Q)^2 at extended (X, Y), Eq. (3) for the Gaussian d orbital.
+// |M(Q)|^2 = F(Q)^2 at extended (X, Y), Eq. (3) for the Gaussian d orbital (rounded
+// alike in every kernel: no contraction left to the compiler).
 __device__ __forceinline__ double form_factor_sq(const double2 fx, const double2 fy, double s)
 {
+#pragma clang fp contract(off)
     const double q2 = fx.y + fy.y;
     const double dq = fx.y - fy.y;
-    const double F = fx.x * fy.x * (1.0 - 2.0 * s * q2 + s * s * dq * dq);
+    const double F = fx.x * fy.x * fma(s * s * dq, dq, fma(-2.0 * s, q2, 1.0));
     return F * F;
 }
 

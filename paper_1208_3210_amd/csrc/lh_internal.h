@@ -247,6 +247,9 @@ inline bool se_cols(const Geo &g) { return g.even && !g.bs && g.logNy >= (g.fp64
 hipError_t launch_se_group(const Plan *const *pls, int n, const EvenInst *d_desc, int pass, hipStream_t st);
 hipError_t launch_se1(const Plan &pl, void *spec, int band, int acc, hipStream_t st);
 hipError_t launch_secol(const Plan &pl, void *spec, int n, bool inv, hipStream_t st);
+// The extended maps of the RPA path (lh_maps.hip).
+hipError_t launch_extend(const Plan &pl, void *out, hipStream_t st);
+hipError_t launch_rpa_map(const Plan &pl, int vkind, double V, void *re, void *imr, void *rer, hipStream_t st);
 hipError_t launch_p3f(const Plan &pl, hipStream_t st);  // general path: window by FFT along energy
 hipError_t launch_cut(const Plan &pl, const void *im, const int *xy, int npts, void *out, hipStream_t st);
 // res: 3 + 4 * nseg doubles of device memory; im_plane: the plane to cut

@@ -1568,64 +1568,6 @@ __global__ void __launch_bounds__(kE5MaxThreads) k_e5_batch(const EvenInst *__re
                             d.ffx, d.ffy, (T *)d.out, d.onx, d.ony, (const T *)nullptr, 0);
 }
 
-// First-zone value at lag m (0 outside 1 <= m < neps), and the blend
-// (1 - f) value(m) + f value(m + 1) in FP64 for an omega between two lags.
-template <typename T>
-__device__ __forceinline__ T lag_value(const T *__restrict__ im1, size_t nk, size_t q, int neps, long m)
-{
-    const bool in = m >= 1 && m < neps;
-    const T x = im1[(size_t)(in ? m : 1) * nk + q];
-    return in ? x : (T)0;
-}
-template <typename T>
-__device__ __forceinline__ double lag_blend(const T *__restrict__ im1, size_t nk, size_t q, int neps, long m,
-                                            double f)
-{
-    return (1.0 - f) * (double)lag_value(im1, nk, q, neps, m) + f * (double)lag_value(im1, nk, q, neps, m + 1);
-}
-
-// Extended, form-factor weighted map from the first-zone planes (RPA path).
-template <typename T>
-__global__ void __launch_bounds__(kThreads) k_extend(const T *__restrict__ im1, int nkx, int nky, int nkz, int neps,
-                                                    const int *__restrict__ lags, const double *__restrict__ fracs,
-                                                    int nw, int zx, int zy, int ff, double ffs,
-                                                    const double2 *__restrict__ ffx, const double2 *__restrict__ ffy,
-                                                    T *__restrict__ out, int out_nx, int out_ny)
-{
-    // one thread per first-zone point (u, v) and group of four planes: the
-    // first-zone values are read once and written to every zone image.  In
-    // three dimensions v runs over nkz planes of nky rows (natural order);
-    // plane z goes to the output block (z + nkz/2) mod nkz of zy * nky rows.
-    const int u = blockIdx.x * kThreads + threadIdx.x;
-    const int v = blockIdx.y;
-    const int w0 = blockIdx.z * 4;
-    if (u >= nkx) return;
-    const size_t nk = (size_t)nkx * nky * nkz, q = (size_t)v * nkx + u;
-    T vals[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int w = min(w0 + i, nw - 1);
-        const double f = fracs[w];
-        vals[i] = f > 0.0 ? (T)lag_blend(im1, nk, q, neps, lags[w], f) : lag_value(im1, nk, q, neps, lags[w]);
-    }
-    const size_t plane = (size_t)out_nx * out_ny;
-    // (any grid size: modulo rather than masks)
-    const int vy = v % nky, vz = v / nky;
-    const int Yz = ((vz + nkz / 2) % nkz) * zy * nky;  // first row of the output block
-    const int xu = (u + (zx * nkx) / 2) % nkx, yv = (vy + (zy * nky) / 2) % nky;
-    for (int zi = 0; zi < zy; ++zi) {
-        const int Yb = zi * nky + yv, Y = Yz + Yb;
-        for (int zj = 0; zj < zx; ++zj) {
-            const int X = zj * nkx + xu;
-            const double m2 = ff ? form_factor_sq(ffx[X], ffy[Yb], ffs) : 1.0;
-            const size_t o0 = (size_t)Y * out_nx + X;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (w0 + i < nw) out[(size_t)(w0 + i) * plane + o0] = ff ? (T)((double)vals[i] * m2) : vals[i];
-        }
-    }
-}
-
 // Kramers-Kronig on the matrix cores: re1[slot][q] = sum_j w(lag, j) im1[j][q]
 // for every needed lag, with FP64 products and sums (v_mfma_f64_16x16x4f64).
 // The weights vanish unless j - lag is odd, so the lags come in tiles of 16
@@ -1725,83 +1667,6 @@ __global__ void __launch_bounds__(64 * WV) k_kkm(const T *__restrict__ im1, int 
 #pragma unroll
         for (int qt = 0; qt < 8; ++qt)
             if (q0 + 16 * qt + qcol < nk) dst[16 * qt] = (T)acc[qt][r];
-    }
-}
-
-// RPA epilogue on the extended map: chi = |M|^2 (Re + i Im),
-// chi_RPA = chi / (1 - V chi) with a contact (vkind 0) or Coulomb (vkind 1)
-// interaction, FP64 arithmetic, rounded once to T.
-template <typename T>
-__global__ void __launch_bounds__(kThreads) k_rpa(const T *__restrict__ im1, const T *__restrict__ re1, int nkx,
-                                                 int nky, int neps, const int *__restrict__ lags,
-                                                 const double *__restrict__ fracs,
-                                                 const int *__restrict__ kkslot, int nw, int zx,
-                                                 int zy, int ff, double ffs, const double2 *__restrict__ ffx,
-                                                 const double2 *__restrict__ ffy, int vkind, double V, int kzn,
-                                                 T *__restrict__ re_out, T *__restrict__ imr, T *__restrict__ rer,
-                                                 int out_nx, int out_ny, int nkz)
-{
-    // one thread per first-zone point (u, v) and group of four planes: the
-    // first-zone Im / Re are read once and every zone image is written (in
-    // three dimensions as in k_extend: v over nkz planes of nky rows)
-    const int u = blockIdx.x * kThreads + threadIdx.x;
-    const int v = blockIdx.y;
-    const int w0 = blockIdx.z * 4;
-    if (u >= nkx) return;
-    const size_t q = (size_t)v * nkx + u, nk = (size_t)nkx * nky * nkz;
-    double imv[4], rev[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int w = min(w0 + i, nw - 1);
-        const double f = fracs[w];
-        imv[i] = f > 0.0 ? (double)(T)lag_blend(im1, nk, q, neps, lags[w], f)
-                         : (double)lag_value(im1, nk, q, neps, lags[w]);
-        // Re chi at the omega: its lag's plane, or the blend of two lags
-        const int sa = kkslot[2 * w], sb = kkslot[2 * w + 1];
-        const double ra = (double)re1[(size_t)sa * nk + q];
-        rev[i] = f > 0.0 && sb >= 0 ? (double)(T)((1.0 - f) * ra + f * (double)re1[(size_t)sb * nk + q]) : ra;
-    }
-    const size_t plane = (size_t)out_nx * out_ny;
-    const int vy = v % nky, vz = v / nky;
-    const int Zc = (vz + nkz / 2) % nkz, Yz = Zc * zy * nky;
-    // kz in reciprocal-lattice units of the third axis (0 in two dimensions)
-    const double hz = (double)(Zc - nkz / 2) / nkz;
-    const int xu = (u + (zx * nkx) / 2) % nkx, yv = (vy + (zy * nky) / 2) % nky;
-    for (int zi = 0; zi < zy; ++zi) {
-        const int Yb = zi * nky + yv, Y = Yz + Yb;
-        for (int zj = 0; zj < zx; ++zj) {
-            const int X = zj * nkx + xu;
-            // interaction: contact U = V, or Coulomb V / |Q|^2 with
-            // Q = 2 pi (h, l, hz) in units of 1/a (h, l the reciprocal-lattice
-            // coordinates of X, Y: a grid spanning kzn zones has a step of
-            // kzn / n; hz that of the kz plane, lattice constant a along z
-            // too); at Q = 0 chi_RPA -> -1/V -> 0
-            double U = V;
-            bool q0 = false;
-            if (vkind == 1) {
-                const double h = (double)kzn * (X - (zx * nkx) / 2) / nkx, l = (double)kzn * (Yb - (zy * nky) / 2) / nky;
-                const double q2 = (2.0 * kPi) * (2.0 * kPi) * (h * h + l * l + hz * hz);
-                q0 = q2 == 0.0;
-                U = q0 ? 0.0 : V / q2;
-            }
-            const double m2 = ff ? form_factor_sq(ffx[X], ffy[Yb], ffs) : 1.0;
-            const size_t o0 = (size_t)Y * out_nx + X;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (w0 + i >= nw) break;
-                double im = imv[i], re = rev[i];
-                if (ff) {
-                    im = (double)(T)(im * m2);
-                    re = (double)(T)(re * m2);
-                }
-                const double a = 1.0 - U * re, b = U * im;
-                const double inv = 1.0 / (a * a + b * b);
-                const size_t o = (size_t)(w0 + i) * plane + o0;
-                if (re_out) re_out[o] = (T)re;
-                if (imr) imr[o] = q0 ? (T)0 : (T)(im * inv);
-                if (rer) rer[o] = q0 ? (T)0 : (T)((re * a - U * im * im) * inv);
-            }
-        }
     }
 }
 
@@ -2671,10 +2536,7 @@ static hipError_t exec_bs(const Plan &pl, T *out, hipStream_t st, hipEvent_t *ev
             LH_SWITCH_LOGM(g.logMx, LH_B5)
 #undef LH_B5
         }
-        const int ff = pl.p.ff_kind != LINDHARD_FF_NONE;
-        hipLaunchKernelGGL(k_extend<T>, dim3(cdiv(g.nkx, kThreads), g.nky, cdiv(pl.p.nomega, 4)), dim3(kThreads), 0,
-                           st, (const T *)pl.im1, g.nkx, g.nky, 1, g.neps, pl.d_lag, pl.d_frac, pl.p.nomega, pl.zx,
-                           pl.zy, ff, pl.ff_s, pl.ffx, pl.ffy, out, pl.out_nx, pl.out_ny);
+        LH_HIP_TRY(launch_extend(pl, out, st));
     } else if (g.even) {
         LH_HIP_TRY(launch_even_any(pl, 5, out, st));
     } else {
@@ -2694,7 +2556,6 @@ static hipError_t exec_t(const Plan &pl, T *out, hipStream_t st, hipEvent_t *ev)
 {
     const Geo &g = pl.g;
     if (g.bs) return exec_bs<T>(pl, out, st, ev);
-    const int ff = pl.p.ff_kind != LINDHARD_FF_NONE;
     auto mark = [&](int i) {
         if (ev) (void)hipEventRecord(ev[i], st);
     };
@@ -2885,10 +2746,7 @@ static hipError_t exec_t(const Plan &pl, T *out, hipStream_t st, hipEvent_t *ev)
         mark(4);
         if (!pl.p.want_rpa) LH_HIP_TRY(p5(pl.spec));  // every plane is zero
     }
-    if (pl.p.want_rpa)
-        hipLaunchKernelGGL(k_extend<T>, dim3(cdiv(g.nkx, kThreads), g.nky * g.nkz, cdiv(pl.p.nomega, 4)),
-                           dim3(kThreads), 0, st, (const T *)pl.im1, g.nkx, g.nky, g.nkz, g.neps, pl.d_lag, pl.d_frac,
-                           pl.p.nomega, pl.zx, pl.zy, ff, pl.ff_s, pl.ffx, pl.ffy, out, pl.out_nx, pl.out_ny);
+    if (pl.p.want_rpa) LH_HIP_TRY(launch_extend(pl, out, st));
     mark(5);
     return hipGetLastError();
 }
@@ -3147,11 +3005,7 @@ static hipError_t rpa_t(const Plan &pl, int vkind, double U, T *re, T *imr, T *r
     else
         hipLaunchKernelGGL((k_kkm<T, 4>), dim3(cdiv(nk, kKkQ), 1), dim3(256), 0, st, (const T *)pl.im1, nk, g.neps,
                            pl.kkw, pl.d_kkrow, pl.kk_ntiles, pl.kk_nch, (T *)pl.re1);
-    const int ff = pl.p.ff_kind != LINDHARD_FF_NONE;
-    hipLaunchKernelGGL(k_rpa<T>, dim3(cdiv(g.nkx, kThreads), g.nky * g.nkz, cdiv(pl.p.nomega, 4)), dim3(kThreads), 0,
-                       st, (const T *)pl.im1, (const T *)pl.re1, g.nkx, g.nky, g.neps, pl.d_lag, pl.d_frac,
-                       pl.d_kkslot, pl.p.nomega, pl.zx, pl.zy, ff, pl.ff_s, pl.ffx, pl.ffy, vkind, U, pl.p.k_zones, re,
-                       imr, rer, pl.out_nx, pl.out_ny, g.nkz);
+    LH_HIP_TRY(launch_rpa_map(pl, vkind, U, re, imr, rer, st));
     return hipGetLastError();
 }
 
