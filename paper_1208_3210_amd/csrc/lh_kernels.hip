@@ -2655,7 +2655,15 @@ static hipError_t exec_t(const Plan &pl, T *out, hipStream_t st, hipEvent_t *ev)
     };
     const size_t plane_out = (size_t)pl.out_nx * pl.out_ny;
     mark(0);
-    if (g.nL > 0 && !pl.pairs && !(pl.has_m2 && pl.nb > 1)) {
+    if (g.nL > 0 && even_small(g) && pl.nb == 1 && !pl.pairs && !pl.has_m2) {
+        LH_HIP_TRY(launch_small_fwd(pl, st));
+        mark(1);
+        mark(2);
+        LH_HIP_TRY(window_t<T>(pl, st));
+        mark(3);
+        mark(4);
+        LH_HIP_TRY(launch_small_inv(pl, out, st));
+    } else if (g.nL > 0 && !pl.pairs && !(pl.has_m2 && pl.nb > 1)) {
         for (int b = 0; b < pl.nb; ++b) LH_HIP_TRY(p1(pl.spec, b, b > 0));
         mark(1);
         LH_HIP_TRY(col(pl.spec, g.nS, false));
@@ -2911,7 +2919,9 @@ static hipError_t even_group_t(const Plan *const *pls, int n, const EvenInst *d,
         else                                                                                                        \
             hipLaunchKernelGGL((k_e1_batch<T, LG, false>), grid, dim3(g.e1_R * F::G), lds, st, d);                  \
     } while (0)
-    if (se_rows(g)) {
+    if (even_small(g)) {
+        LH_HIP_TRY(launch_small_group(pls, n, d, false, st));
+    } else if (se_rows(g)) {
         LH_HIP_TRY(launch_se_group(pls, n, d, 1, st));
     } else {
         LH_SWITCH_LOG9(g.logNx, LH_E1B)
@@ -2936,7 +2946,7 @@ static hipError_t even_group_t(const Plan *const *pls, int n, const EvenInst *d,
 #undef LH_ECB
         return hipGetLastError();
     };
-    LH_HIP_TRY(col(nS, false));
+    if (!even_small(g)) LH_HIP_TRY(col(nS, false));
     // P3
     if (g.e3_variant == 2) {
         if constexpr (sizeof(T) == 4) {
@@ -2965,6 +2975,7 @@ static hipError_t even_group_t(const Plan *const *pls, int n, const EvenInst *d,
 #undef LH_E3B
         LH_HIP_TRY(hipGetLastError());
     }
+    if (even_small(g)) return launch_small_group(pls, n, d, true, st);
     LH_HIP_TRY(col(nL, true));
     // P5
 #define LH_E5B(LG)                                                                                                  \

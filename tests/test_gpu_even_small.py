@@ -1,0 +1,72 @@
+"""Small square grids, a slice per block (both forward transforms in one kernel, both
+inverse transforms and the output in another), against the general path on the
+same problem (the band symmetry not used): the smallest and largest sizes of each
+type, momentum-density weights, several zones with the form factor, omegas between
+lags and past the band, the RPA planes, unaligned outputs, a batch of unlike
+instances.  Tolerance: the sum of both paths' tolerances of the hot path."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1208_3210_amd import lindhard as LH
+from paper_1208_3210_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+TOL = {LH.LINDHARD_FP64: 1e-11, LH.LINDHARD_FP32C: 1e-5}
+PRECS = [LH.LINDHARD_FP64, LH.LINDHARD_FP32C]
+SIZES = [16, 32, 64, 128]
+FORMS = {
+    "plain": {},
+    "rho": dict(rho=True),
+    "zones": dict(zones=(5, 3), ff_kind=LH.LINDHARD_FF_GAUSS_DX2Y2, ff_width=0.6),
+    "between": dict(omega=[0.5, 1, 2.25, 7, 30.75, 31, 62.5, 63], omega_interp=True),
+    "rpa": dict(want_rpa=True, zones=(1, 3)),
+    "narrow": dict(emin=-0.4, emax=2.4),
+}
+
+
+def config(n, prec, form):
+    f = dict(FORMS[form])
+    emin, emax = f.pop("emin", -1.6), f.pop("emax", 1.6)
+    lags = np.asarray(f.pop("omega", [0, 1, 2, 15, 16, 40, 63]), dtype=np.float64)
+    if f.pop("rho", False):
+        f["rho_table"] = W.momentum_density_dx2y2(n, n, 1, 0.6)
+    return dict(W.seeded_band(np.random.Generator(np.random.PCG64(n))), filling=1.1, nkx=n, nky=n, neps=64,
+                emin=emin, emax=emax, gamma=0.08, omega=lags * ((emax - emin) / 64), precision=prec, **f)
+
+
+def maps(cfg):
+    plan = LH.Plan(**cfg)
+    out = [plan.exec()] + (list(plan.rpa(0.5)) if cfg.get("want_rpa") else [])
+    sched = plan.info.schedule.decode()
+    buf = torch.full((out[0].numel() + 2,), 7.0, dtype=out[0].dtype, device="cuda")
+    LH.lindhard_exec(plan.handle, buf[1:].data_ptr(), torch.cuda.current_stream().cuda_stream)
+    assert torch.equal(buf[1:-1], out[0].flatten()) and buf[0] == 7.0 and buf[-1] == 7.0
+    out = [o.double().cpu() for o in out]
+    plan.close()
+    return out, sched
+
+
+@pytest.mark.parametrize("form", list(FORMS))
+@pytest.mark.parametrize("n", SIZES)
+@pytest.mark.parametrize("prec", PRECS)
+def test_small_against_general_path(prec, n, form, monkeypatch):
+    cfg = config(n, prec, form)
+    got, sched = maps(cfg)
+    assert " even " in sched
+    monkeypatch.setenv("LINDHARD_SYMMETRY", "off")
+    ref, sched = maps(cfg)
+    assert " even " not in sched
+    for a, b in zip(got, ref):
+        assert float((a - b).abs().max()) <= 2 * TOL[prec] * float(b.abs().max())
+
+
+@pytest.mark.parametrize("prec,n", [(LH.LINDHARD_FP64, 32), (LH.LINDHARD_FP32C, 128)])
+def test_small_batch_is_bitwise_the_single_call(prec, n):
+    plans = [LH.Plan(**dict(config(n, prec, f), gamma=0.06 + 0.01 * i))
+             for i, f in enumerate(["plain", "zones", "between", "narrow", "plain"])]
+    outs = LH.exec_batch(plans)
+    for p, o in zip(plans, outs):
+        assert torch.equal(p.exec(), o)
+        p.close()
