@@ -34,6 +34,22 @@ __device__ __forceinline__ double form_factor_sq(const double2 fx, const double2
     return F * F;
 }
 
+// Store of an output map by the last row passes.  NT: past the caches, which then
+// keep the spectra that the pass reads; from rows of 1024 points on (two bands
+// 1024^2 x 129 lags: 171 -> 144 us for the pass, 2048^2 x 256 FP64: 2.20 -> 2.14 ms,
+// 1024 x 512 x 128 with a caller's band: 130 -> 117; at 512^2 x 64 a call takes 93 and
+// 95 us, at 256^2 x 64 with 3 x 3 zones 69 and 94).
+template <bool NT, typename T>
+__device__ __forceinline__ void store_map(T *p, T v)
+{
+    if constexpr (!NT) {
+        *p = v;
+    } else {
+        typedef unsigned nt_bits __attribute__((ext_vector_type(sizeof(T) / 4)));
+        __builtin_nontemporal_store(__builtin_bit_cast(nt_bits, v), reinterpret_cast<nt_bits *>(p));
+    }
+}
+
 // A zero the optimiser cannot see through.  Added to a thread's position in
 // a loop body it keeps the loads and LDS addresses that depend on it inside
 // the loop, rather than hoisted out and held in registers across it.

@@ -1,0 +1,42 @@
+"""Output maps of rows that the last row pass writes past the caches (1024 points on)
+and of the largest rows that it does not: the value of every point does not depend on the
+buffer's alignment, nothing beside the map is written, and the maps agree with the
+oracle on sampled columns of the transform (bitwise for the former, the hot path's
+tolerance for the latter)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1208_3210_amd import lindhard as LH
+from paper_1208_3210_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+TOL = {LH.LINDHARD_FP64: 1e-11, LH.LINDHARD_FP32C: 1e-5}
+
+
+@pytest.mark.parametrize("prec", [LH.LINDHARD_FP64, LH.LINDHARD_FP32C])
+@pytest.mark.parametrize("even", [True, False])
+@pytest.mark.parametrize("nkx", [512, 1024])
+def test_map_stores(nkx, even, prec):
+    nky, neps, lags = 8, 32, [1, 2, 9, 30]
+    rng = np.random.Generator(np.random.PCG64(nkx))
+    tab = rng.uniform(-1.2, 1.3, size=(nky, nkx))
+    if even:
+        tab = tab + tab[:, -np.arange(nkx) % nkx]
+        tab = (tab + tab[-np.arange(nky) % nky]) / 4
+    cfg = dict(eps_table=tab, mu=0.05, nkx=nkx, nky=nky, neps=neps, emin=-1.5, emax=1.5, gamma=0.1,
+               omega=np.array(lags) * (3.0 / neps), precision=prec, zones=(1, 3))
+    plan = LH.Plan(**cfg)
+    assert (" even " in plan.info.schedule.decode()) == even
+    ref = plan.exec()
+    full = oracle.chi_full(tab - 0.05, neps, -1.5, 1.5, 0.1, np.array(lags))
+    want = oracle.extend(full, 1, 3, 0, 0.0)
+    assert np.abs(ref.double().cpu().numpy() - want).max() <= TOL[prec] * np.abs(want).max()
+    for off in (1, 2, 3):
+        buf = torch.full((ref.numel() + 8,), 7.0, dtype=ref.dtype, device="cuda")
+        LH.lindhard_exec(plan.handle, buf[off:].data_ptr(), torch.cuda.current_stream().cuda_stream)
+        assert torch.equal(buf[off:off + ref.numel()], ref.flatten())
+        assert torch.all(buf[:off] == 7.0) and torch.all(buf[off + ref.numel():] == 7.0)
+    plan.close()
