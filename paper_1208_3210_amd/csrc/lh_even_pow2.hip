@@ -122,13 +122,13 @@ __device__ __forceinline__ void se_forward(cx<T> *v, cx<T> *line1, cx<T> *line2,
 // thread, see kSeWaves32).  A block's L consecutive rows fill whole 128-byte lines
 // of the tiles (one row at four pairs instead: 0.72 against 0.63 ms; in FP64 3.05
 // against 1.43), or with fewer than four rows the blocks of a line run on one XCD.
-template <typename T, int LOGN, bool W>
+template <typename T, int LOGN, bool W, bool PAST = false>
 __device__ __forceinline__ void se1_body(const double *__restrict__ xi, const Geo &g, double emin, double deps,
                                          double gamma, const cx<T> *__restrict__ tab, T *__restrict__ spec,
                                          const T *__restrict__ rho, int acc, int jc)
 {
     using F = EvenFFT<T, LOGN>;
-    constexpr int L = se_lines<T, LOGN>(), NT = se_threads<T, LOGN>(), LS = se_stride<T, LOGN>(false);
+    constexpr int L = se_lines<T, LOGN>(), TH = se_threads<T, LOGN>(), LS = se_stride<T, LOGN>(false);
     constexpr int N = F::N;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cx<T> *lds = reinterpret_cast<cx<T> *>(smem_raw), *t2 = lds + L * LS;
@@ -142,7 +142,7 @@ __device__ __forceinline__ void se1_body(const double *__restrict__ xi, const Ge
     constexpr int VEC = 16 / sizeof(T), Ce = 2 * VEC;
     // tiles stored side by side: their columns a multiple of 16, so that the
     // staged positions advance by a constant
-    constexpr int TS = NT / (2 * L) & ~(16 / Ce - 1);
+    constexpr int TS = TH / (2 * L) & ~(16 / Ce - 1);
     const int h = tid & 1, r = (tid >> 1) % L, tile0 = (tid >> 1) / L;
     const int row = ky0 + r;
     for (int j = jbeg; j < jend; j += 2) {
@@ -196,8 +196,8 @@ __device__ __forceinline__ void se1_body(const double *__restrict__ xi, const Ge
                         b.v[i] += ob.v[i];
                     }
                 }
-                *pa = __builtin_bit_cast(lh_u4, a);
-                if (two) *pb = __builtin_bit_cast(lh_u4, b);
+                store_past<PAST>(pa, __builtin_bit_cast(lh_u4, a));
+                if (two) store_past<PAST>(pb, __builtin_bit_cast(lh_u4, b));
             }
         }
         __syncthreads();
@@ -208,12 +208,12 @@ __device__ __forceinline__ void se1_body(const double *__restrict__ xi, const Ge
 // three on one SIMD, so two blocks per CU (18 waves) need room for six.
 constexpr int kSeWaves32 = 6;
 
-template <typename T, int LOGN, bool W>
+template <typename T, int LOGN, bool W, bool PAST>
 __global__ void __launch_bounds__((se_threads<T, LOGN>()), (sizeof(T) == 4 ? kSeWaves32 : 2))
     k_se1(const double *__restrict__ xi, Geo g, double emin, double deps, double gamma, const cx<T> *__restrict__ tab,
           T *__restrict__ spec, const T *__restrict__ rho, int acc, int jc)
 {
-    se1_body<T, LOGN, W>(xi, g, emin, deps, gamma, tab, spec, rho, acc, jc);
+    se1_body<T, LOGN, W, PAST>(xi, g, emin, deps, gamma, tab, spec, rho, acc, jc);
 }
 template <typename T, int LOGN, bool W>
 __global__ void __launch_bounds__((se_threads<T, LOGN>()), (sizeof(T) == 4 ? kSeWaves32 : 2))
@@ -228,7 +228,7 @@ __global__ void __launch_bounds__((se_threads<T, LOGN>()), (sizeof(T) == 4 ? kSe
 // P2 (INV false), P4 (INV true): each line is a pair of neighbouring real columns
 // of a tile (one complex value per row), the lines of a tile interleaved lane by
 // lane so that a wave's loads and stores cover whole tile rows.  In place.
-template <typename T, int LOGN, bool INV>
+template <typename T, int LOGN, bool INV, bool PAST = false>
 __device__ __forceinline__ void secol_body(T *__restrict__ spec, const Geo &g, const cx<T> *__restrict__ tab)
 {
     using F = EvenFFT<T, LOGN>;
@@ -260,13 +260,14 @@ __device__ __forceinline__ void secol_body(T *__restrict__ spec, const Geo &g, c
     const unsigned oo = (unsigned)(tile * g.HyS * C + c + n0 * C);
 #pragma unroll
     for (int i = 0; i < 16; ++i)
-        if (i < i1 && n0 + 8 * F::R3 * i >= nlo) *at32(base, oo + 8 * F::R3 * i * C) = zp[9 * F::R3 * i];
+        if (i < i1 && n0 + 8 * F::R3 * i >= nlo)
+            store_past<PAST>(at32(base, oo + 8 * F::R3 * i * C), zp[9 * F::R3 * i]);
 }
-template <typename T, int LOGN, bool INV>
+template <typename T, int LOGN, bool INV, bool PAST>
 __global__ void __launch_bounds__((se_threads<T, LOGN>()), (sizeof(T) == 4 ? kSeWaves32 : 2))
     k_secol(T *__restrict__ spec, Geo g, const cx<T> *__restrict__ tab)
 {
-    secol_body<T, LOGN, INV>(spec, g, tab);
+    secol_body<T, LOGN, INV, PAST>(spec, g, tab);
 }
 template <typename T, int LOGN, bool INV>
 __global__ void __launch_bounds__((se_threads<T, LOGN>()), (sizeof(T) == 4 ? kSeWaves32 : 2))
@@ -297,6 +298,17 @@ int se1_jc()
     return LOGN >= 11 ? 4 : 1;
 }
 
+// Slices of 1 GB and more in all, four times the last-level cache, are stored past
+// the caches: the next pass starts at their beginning, which is evicted by then
+// either way, and the pass's own reads stay.  2048^2 x 512 x 256, ms: builder
+// 0.64 -> 0.61, P2 0.76 -> 0.71, P4 0.43 -> 0.42, FP64 1.44 -> 1.41, 1.48 -> 1.40 and 0.86 ->
+// 0.83.  A call with 134 MB of slices (2048^2, 16 lags) would go 259 -> 274 us, one with
+// 0.5 GB of FP64 ones 973 -> 997.
+inline bool se_past(const Geo &g, int slices)
+{
+    return (size_t)slices * g.slice_e * (g.fp64 ? 8 : 4) >= (size_t)1 << 30;
+}
+
 template <typename T>
 hipError_t se1_t(const Plan &pl, T *spec, int band, int acc, hipStream_t st)
 {
@@ -308,7 +320,10 @@ hipError_t se1_t(const Plan &pl, T *spec, int band, int acc, hipStream_t st)
         constexpr int L = se_lines<T, LG>(), GR = L < 4 ? 4 / L : 1;                                                 \
         const int jc = se1_jc<T, LG>();                                                                              \
         const dim3 grid(cdiv(cdiv(g.Hy, L), 8 * GR) * 8 * GR, cdiv(pairs, jc));                                \
-        const auto k = pl.rho ? &k_se1<T, LG, true> : &k_se1<T, LG, false>;                                          \
+        constexpr bool P = LG >= 11; /* shorter axes: plain stores only */                                          \
+        const bool past = P && se_past(g, g.nS);                                                                     \
+        const auto k = pl.rho ? (past ? &k_se1<T, LG, true, P> : &k_se1<T, LG, true, false>)                         \
+                              : (past ? &k_se1<T, LG, false, P> : &k_se1<T, LG, false, false>);                      \
         hipLaunchKernelGGL(k, grid, dim3(se_threads<T, LG>()), (se_lds<T, LG>(false)), st, pl.xi + band * nk, g,     \
                            pl.p.emin, pl.deps, pl.p.gamma, (const cx<T> *)pl.evx, spec,                              \
                            pl.rho ? (const T *)pl.rho + band * nk : nullptr, acc, jc);                               \
@@ -326,7 +341,10 @@ hipError_t secol_t(const Plan &pl, T *spec, int n, bool inv, hipStream_t st)
     do {                                                                                                             \
         constexpr int TB = se_lines<T, LG>() / (16 / (int)sizeof(T));                                                \
         const dim3 grid(cdiv(g.NTe, TB), n);                                                                         \
-        const auto k = inv ? &k_secol<T, LG, true> : &k_secol<T, LG, false>;                                         \
+        constexpr bool P = LG >= 11; /* shorter axes: plain stores only */                                          \
+        const bool past = P && se_past(g, n);                                                                        \
+        const auto k = inv ? (past ? &k_secol<T, LG, true, P> : &k_secol<T, LG, true, false>)                        \
+                           : (past ? &k_secol<T, LG, false, P> : &k_secol<T, LG, false, false>);                     \
         hipLaunchKernelGGL(k, grid, dim3(se_threads<T, LG>()), (se_lds<T, LG>(true)), st, spec, g,                   \
                            (const cx<T> *)pl.evy);                                                            \
     } while (0)

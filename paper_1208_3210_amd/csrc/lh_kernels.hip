@@ -609,7 +609,7 @@ __global__ void __launch_bounds__(kThreads) k_p5(const cx<T> *__restrict__ spec,
                             b += o.y;
                         }
                     }
-                    store_map<(LOGL >= 9)>(reinterpret_cast<cx<T> *>(orow + X), mk<T>(a, b));
+                    store_past<(LOGL >= 9)>(reinterpret_cast<cx<T> *>(orow + X), mk<T>(a, b));
                 }
             }
         }
@@ -1534,7 +1534,7 @@ __device__ __forceinline__ void e5_body(const T *__restrict__ spec, const Geo &g
                                 val = (T)((double)val * (double)m2[(size_t)Y * out_nx + X]);
                                 if (acc) val += orow[X];
                             }
-                            store_map<(LOGNX >= 10)>(orow + X, val);
+                            store_past<(LOGNX >= 10)>(orow + X, val);
                         }
                     }
                 }

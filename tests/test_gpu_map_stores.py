@@ -2,7 +2,8 @@
 and of the largest rows that it does not: the value of every point does not depend on the
 buffer's alignment, nothing beside the map is written, and the maps agree with the
 oracle on sampled columns of the transform (bitwise for the former, the hot path's
-tolerance for the latter)."""
+tolerance for the latter).  Slices of 1 GB and more, which the builder and the column
+passes store past the caches: bitwise the batched call, which does not."""
 import numpy as np
 import pytest
 import torch
@@ -40,3 +41,15 @@ def test_map_stores(nkx, even, prec):
         assert torch.equal(buf[off:off + ref.numel()], ref.flatten())
         assert torch.all(buf[:off] == 7.0) and torch.all(buf[off + ref.numel():] == 7.0)
     plan.close()
+
+
+@pytest.mark.parametrize("prec,lags", [(LH.LINDHARD_FP32C, [1, 256]), (LH.LINDHARD_FP64, [1, 128])])
+def test_large_slices(prec, lags):
+    cfg = dict(filling=1.1, nkx=2048, nky=2048, neps=512, emin=-2.0, emax=2.0, gamma=0.02,
+               omega=np.array(lags) * (4.0 / 512), precision=prec, **W.seeded_band(np.random.Generator(np.random.PCG64(3))))
+    plan, other = LH.Plan(**cfg), LH.Plan(**dict(cfg, gamma=0.03))
+    first = plan.exec().clone()
+    assert torch.equal(first, LH.exec_batch([plan, other])[0])
+    assert torch.equal(first, plan.exec())
+    plan.close()
+    other.close()
