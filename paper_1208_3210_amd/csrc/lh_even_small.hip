@@ -284,15 +284,17 @@ __global__ void __launch_bounds__((Small<T, LOGN>::NT)) k_small_inv_batch(const 
     }
 
 template <typename T>
-hipError_t fwd_t(const Plan &pl, hipStream_t st)
+hipError_t fwd_t(const Plan &pl, T *spec, int band, hipStream_t st)
 {
     const Geo &g = pl.g;
+    const size_t nk = (size_t)g.nkx * g.nky;
 #define LH_SF(LG)                                                                                                    \
     do {                                                                                                             \
         using S = Small<T, LG>;                                                                                      \
         const auto k = pl.rho ? &k_small_fwd<T, LG, true> : &k_small_fwd<T, LG, false>;                              \
-        hipLaunchKernelGGL(k, dim3(g.nS), dim3(S::NT), S::LDS, st, pl.xi, g, pl.p.emin, pl.deps, pl.p.gamma,         \
-                           (const cx<T> *)pl.twx, (T *)pl.spec, (const T *)pl.rho);                                  \
+        hipLaunchKernelGGL(k, dim3(g.nS), dim3(S::NT), S::LDS, st, pl.xi + band * nk, g, pl.p.emin, pl.deps,         \
+                           pl.p.gamma, (const cx<T> *)pl.twx, spec,                                                  \
+                           pl.rho ? (const T *)pl.rho + band * nk : nullptr);                                        \
     } while (0)
     LH_SMALL_SWITCH(g.logNx, LH_SF)
 #undef LH_SF
@@ -300,7 +302,7 @@ hipError_t fwd_t(const Plan &pl, hipStream_t st)
 }
 
 template <typename T>
-hipError_t inv_t(const Plan &pl, T *out, hipStream_t st)
+hipError_t inv_t(const Plan &pl, const T *spec, T *out, hipStream_t st)
 {
     const Geo &g = pl.g;
     const int ff = pl.p.ff_kind != LINDHARD_FF_NONE;
@@ -309,7 +311,7 @@ hipError_t inv_t(const Plan &pl, T *out, hipStream_t st)
     do {                                                                                                             \
         using S = Small<T, LG>;                                                                                      \
         const auto k = rpa ? &k_small_inv<T, LG, 1> : &k_small_inv<T, LG, 0>;                                        \
-        hipLaunchKernelGGL(k, dim3(rpa ? g.nL : pl.p.nomega), dim3(S::NT), S::LDS, st, (const T *)pl.spec, g,        \
+        hipLaunchKernelGGL(k, dim3(rpa ? g.nL : pl.p.nomega), dim3(S::NT), S::LDS, st, spec, g,                      \
                            (const cx<T> *)pl.twx, pl.d_src, pl.scale, pl.zx, pl.zy, ff, pl.ff_s, pl.ffx, pl.ffy,     \
                            rpa ? (T *)pl.im1 : out);                                                             \
     } while (0)
@@ -338,14 +340,14 @@ hipError_t group_t(const Plan *const *pls, int n, const EvenInst *d, bool inv, h
 
 }  // namespace
 
-hipError_t launch_small_fwd(const Plan &pl, hipStream_t st)
+hipError_t launch_small_fwd(const Plan &pl, void *spec, int band, hipStream_t st)
 {
-    return pl.g.fp64 ? fwd_t<double>(pl, st) : fwd_t<float>(pl, st);
+    return pl.g.fp64 ? fwd_t<double>(pl, (double *)spec, band, st) : fwd_t<float>(pl, (float *)spec, band, st);
 }
-hipError_t launch_small_inv(const Plan &pl, void *out, hipStream_t st)
+hipError_t launch_small_inv(const Plan &pl, const void *spec, void *out, hipStream_t st)
 {
-    return pl.g.fp64 ? inv_t<double>(pl, (double *)out, st)
-                     : inv_t<float>(pl, (float *)out, st);
+    return pl.g.fp64 ? inv_t<double>(pl, (const double *)spec, (double *)out, st)
+                     : inv_t<float>(pl, (const float *)spec, (float *)out, st);
 }
 hipError_t launch_small_group(const Plan *const *pls, int n, const EvenInst *d, bool inv, hipStream_t st)
 {

@@ -245,14 +245,14 @@ size_t even_any_twiddle_index(int logM, size_t e);
 inline bool se_rows(const Geo &g) { return g.even && !g.bs && g.logNx >= 10; }
 inline bool se_cols(const Geo &g) { return g.even && !g.bs && g.logNy >= (g.fp64 ? 9 : 10); }
 // The even path's transforms of small square grids, a slice per block
-// (lh_even_small.hip): P1 + P2 of a single band, P4 + P5.  Up to 128 points, as
+// (lh_even_small.hip): P1 + P2 of one band (not added to another), P4 + P5.  Up to 128 points, as
 // far as a slice and its lines fit in LDS; faster at every size there.
 inline bool even_small(const Geo &g)
 {
     return g.even && !g.bs && g.nkz == 1 && g.logNx == g.logNy && g.logNx >= 4 && g.logNx <= 7;
 }
-hipError_t launch_small_fwd(const Plan &pl, hipStream_t st);
-hipError_t launch_small_inv(const Plan &pl, void *out, hipStream_t st);
+hipError_t launch_small_fwd(const Plan &pl, void *spec, int band, hipStream_t st);
+hipError_t launch_small_inv(const Plan &pl, const void *spec, void *out, hipStream_t st);
 hipError_t launch_small_group(const Plan *const *pls, int n, const EvenInst *d_desc, bool inv, hipStream_t st);
 hipError_t launch_se_group(const Plan *const *pls, int n, const EvenInst *d_desc, int pass, hipStream_t st);
 hipError_t launch_se1(const Plan &pl, void *spec, int band, int acc, hipStream_t st);

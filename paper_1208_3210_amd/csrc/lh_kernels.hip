@@ -2653,16 +2653,28 @@ static hipError_t exec_t(const Plan &pl, T *out, hipStream_t st, hipEvent_t *ev)
         }
         return hipGetLastError();
     };
+    // the forward passes of every band into bs
+    auto bands = [&](char *bs) -> hipError_t {
+        const bool small = even_small(g);
+        for (int b = 0; b < pl.nb; ++b) {
+            char *d = bs + b * g.nS * sb;
+            LH_HIP_TRY(small ? launch_small_fwd(pl, d, b, st) : p1(d, b, 0));
+        }
+        mark(1);
+        for (int b = 0; b < pl.nb && !small; ++b) LH_HIP_TRY(col(bs + b * g.nS * sb, g.nS, false));
+        mark(2);
+        return hipSuccess;
+    };
     const size_t plane_out = (size_t)pl.out_nx * pl.out_ny;
     mark(0);
     if (g.nL > 0 && even_small(g) && pl.nb == 1 && !pl.pairs && !pl.has_m2) {
-        LH_HIP_TRY(launch_small_fwd(pl, st));
+        LH_HIP_TRY(launch_small_fwd(pl, pl.spec, 0, st));
         mark(1);
         mark(2);
         LH_HIP_TRY(window_t<T>(pl, st));
         mark(3);
         mark(4);
-        LH_HIP_TRY(launch_small_inv(pl, out, st));
+        LH_HIP_TRY(launch_small_inv(pl, pl.spec, out, st));
     } else if (g.nL > 0 && !pl.pairs && !(pl.has_m2 && pl.nb > 1)) {
         for (int b = 0; b < pl.nb; ++b) LH_HIP_TRY(p1(pl.spec, b, b > 0));
         mark(1);
@@ -2681,10 +2693,7 @@ static hipError_t exec_t(const Plan &pl, T *out, hipStream_t st, hipEvent_t *ev)
         // are summed into the output, in a fixed order
         const size_t nocc = (size_t)(g.j0 - g.jA), nb = (size_t)pl.nb;
         char *bs = (char *)pl.bspec, *sp = (char *)pl.spec;
-        for (int b = 0; b < pl.nb; ++b) LH_HIP_TRY(p1(bs + b * g.nS * sb, b, 0));
-        mark(1);
-        for (int b = 0; b < pl.nb; ++b) LH_HIP_TRY(col(bs + b * g.nS * sb, g.nS, false));
-        mark(2);
+        LH_HIP_TRY(bands(bs));
         const size_t nemp = (size_t)g.nS - nocc;
         for (size_t k = 0; k < pl.m2_pairs.size(); ++k) {
             const size_t nu = (size_t)pl.m2_pairs[k] / nb, mu = (size_t)pl.m2_pairs[k] % nb;
@@ -2717,10 +2726,7 @@ static hipError_t exec_t(const Plan &pl, T *out, hipStream_t st, hipEvent_t *ev)
         const size_t nocc = (size_t)(g.j0 - g.jA), nb = (size_t)pl.nb;
         const size_t per = sb / sizeof(T);  // T values per slice
         char *bs = (char *)pl.bspec;
-        for (int b = 0; b < pl.nb; ++b) LH_HIP_TRY(p1(bs + b * g.nS * sb, b, 0));
-        mark(1);
-        for (int b = 0; b < pl.nb; ++b) LH_HIP_TRY(col(bs + b * g.nS * sb, g.nS, false));
-        mark(2);
+        LH_HIP_TRY(bands(bs));
         char *sp = (char *)pl.spec;
         const size_t nemp = (size_t)g.nS - nocc;
         int done = 0;
@@ -2744,9 +2750,9 @@ static hipError_t exec_t(const Plan &pl, T *out, hipStream_t st, hipEvent_t *ev)
             LH_HIP_TRY(launch_lin<T>((T *)pl.sacc, (const T *)pl.spec, 1.0, done++ == 0, (size_t)g.nL * per, st));
         }
         mark(3);
-        LH_HIP_TRY(col(pl.sacc, g.nL, true));
+        if (!even_small(g)) LH_HIP_TRY(col(pl.sacc, g.nL, true));
         mark(4);
-        LH_HIP_TRY(p5(pl.sacc));
+        LH_HIP_TRY(even_small(g) ? launch_small_inv(pl, pl.sacc, out, st) : p5(pl.sacc));
     } else {
         mark(1);
         mark(2);

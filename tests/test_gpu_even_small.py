@@ -70,3 +70,19 @@ def test_small_batch_is_bitwise_the_single_call(prec, n):
     for p, o in zip(plans, outs):
         assert torch.equal(p.exec(), o)
         p.close()
+
+
+@pytest.mark.parametrize("prec,n", [(LH.LINDHARD_FP64, 16), (LH.LINDHARD_FP64, 128), (LH.LINDHARD_FP32C, 32)])
+@pytest.mark.parametrize("form", ["plain", "zones", "between"])
+def test_small_band_pairs_against_general_path(prec, n, form, monkeypatch):
+    """Two bands as weighted pairs: each band's forward passes and the summed windows' inverse ones."""
+    cfg = dict(config(n, prec, form), eps_table=W.multiband_tables(n, 2, seed=n), n_bands=2,
+               pair_weight=np.array([[1.0, 0.5], [0.25, 1.0]]))
+    for k in ("t", "tp", "tpp"):
+        cfg.pop(k, None)
+    got, sched = maps(cfg)
+    assert " even " in sched
+    monkeypatch.setenv("LINDHARD_SYMMETRY", "off")
+    ref, sched = maps(cfg)
+    assert " even " not in sched
+    assert float((got[0] - ref[0]).abs().max()) <= 2 * TOL[prec] * float(ref[0].abs().max())
