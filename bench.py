@@ -31,7 +31,10 @@ KERNEL_NAMES = ["k_p1", "k_col<float, false>", "k_p3", "k_col<float, true>", "k_
 def algorithmic(cfg, lag_hi, even, fp_bytes=4):
     """Algorithmic HBM bytes per pass and flops of the energy window for one
     exec.  General path: complex half plane (nkx/2+1) x nky per slice.  Even
-    path (mirror-symmetric band): real quarter plane (nkx/2+1) x (nky/2+1)."""
+    path (mirror-symmetric band): real quarter plane (nkx/2+1) x (nky/2+1); on
+    square grids the tight-binding band is symmetric under the exchange of kx and
+    ky too, and from 128 points on the window reads and works on half of the
+    points (the forward column pass stores those only) and writes all."""
     n_x, n_y, neps = cfg["nkx"], cfg["nky"], cfg["neps"]
     nw = len(cfg["omega"])
     if even:
@@ -47,10 +50,11 @@ def algorithmic(cfg, lag_hi, even, fp_bytes=4):
     B = pts * nS * vb
     S = pts * nL * vb
     out = n_x * n_y * nw * fp_bytes
-    by = [B, 2 * B, B + S, 2 * S, S + out]
+    half = 0.5 if even and n_x == n_y and n_x >= 128 else 1.0
+    by = [B, B + half * B, half * B + S, 2 * S, S + out]
     j0 = neps // 2
     macs = sum(min(m, j0, neps - m) for m in range(1, nL + 1))
-    fl_win = flops_per_mac * pts * macs
+    fl_win = flops_per_mac * half * pts * macs
     return by, fl_win
 
 
@@ -341,7 +345,7 @@ def bench_general(LH, W, torch, cfg, steps=3):
     """The same 2048^2 x 512 x 256 FP32 instance on the general complex path
     (mirror symmetry not used): complex half-plane slices, 52 bytes per chi
     point of algorithmic traffic (55.9 GB per step) against the even path's
-    16 (17.2 GB); per-pass times, rates and the roofline of its dominant pass."""
+    14 (15.0 GB); per-pass times, rates and the roofline of its dominant pass."""
     old = os.environ.get("LINDHARD_SYMMETRY")
     os.environ["LINDHARD_SYMMETRY"] = "off"
     try:
@@ -572,16 +576,17 @@ def main():
     by, fl_win = algorithmic(cfg, plan.info.lag_hi, even)
     gbs = [b / (t * 1e-3) / 1e9 for b, t in zip(by, pass_avg)]
     dom = int(np.argmax(pass_avg))
-    src = [os.path.join(ROOT, "paper_1208_3210_amd", "csrc", f) for f in ("lh_kernels.hip", "lh_fft.h",
-                                                                           "lh_regfft.h", "lh_window.hip")]
+    csrc = os.path.join(ROOT, "paper_1208_3210_amd", "csrc")
+    src = [os.path.join(csrc, f) for f in sorted(os.listdir(csrc)) if f.endswith((".hip", ".h"))]
     khash = src_hash(src)
     fft_window = " P3 fft " in schedule
     mfma_window = " P3 mfma " in schedule
     mfma4_window = " P3 mfma4 " in schedule
     if even:
-        KERNEL_NAMES[:] = ["k_e1", "k_ecol<float, false>",
+        rows, col = ("k_se1", "k_secol") if cfg["nkx"] >= 1024 else ("k_e1", "k_ecol")
+        KERNEL_NAMES[:] = [rows, col + "<float, false>",
                            "k_e3q" if mfma4_window else "k_e3m" if mfma_window else "k_e3",
-                           "k_ecol<float, true>", "k_e5"]
+                           col + "<float, true>", "k_e5"]
     elif fft_window:
         KERNEL_NAMES[2] = "k_p3f"
     if dom == 2 and not fft_window:
@@ -691,7 +696,7 @@ def main():
                           "even_path_B_per_point": sum(by) / points if even else None,
                           "general_schedule_alg_GB_per_step": sum(algorithmic(cfg, plan.info.lag_hi, False)[0]) / 1e9,
                           "note": "pass rates use the bytes of the path that ran (the even path stores real quarter "
-                                  "planes: 16 B per chi point; the general complex schedule moves 52 B per point)"},
+                                  "planes: 14 B per chi point; the general complex schedule moves 52 B per point)"},
         "general_path": gen, "fp64_gpu": fp64, "batched": batched, "served": served,
         "epilogues": epi, "extended_momentum": ext, "multiband": mb, "k3d": k3, "grid_2049": g2049,
         "grid_4096": g4096,
