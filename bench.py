@@ -28,6 +28,11 @@ PASS_NAMES = ["p1_build_rowfft", "p2_colfft", "p3_window", "p4_colifft", "p5_row
 KERNEL_NAMES = ["k_p1", "k_col<float, false>", "k_p3", "k_col<float, true>", "k_p5"]
 
 
+def window_half(cfg):
+    """Share of the points the even path's window works on (exchange symmetry)."""
+    return 0.5 if cfg["nkx"] == cfg["nky"] and cfg["nkx"] >= 128 else 1.0
+
+
 def algorithmic(cfg, lag_hi, even, fp_bytes=4):
     """Algorithmic HBM bytes per pass and flops of the energy window for one
     exec.  General path: complex half plane (nkx/2+1) x nky per slice.  Even
@@ -50,7 +55,7 @@ def algorithmic(cfg, lag_hi, even, fp_bytes=4):
     B = pts * nS * vb
     S = pts * nL * vb
     out = n_x * n_y * nw * fp_bytes
-    half = 0.5 if even and n_x == n_y and n_x >= 128 else 1.0
+    half = window_half(cfg) if even else 1.0
     by = [B, B + half * B, half * B + S, 2 * S, S + out]
     j0 = neps // 2
     macs = sum(min(m, j0, neps - m) for m in range(1, nL + 1))
@@ -610,12 +615,12 @@ def main():
     passes["p3_window"]["TFLOP/s"] = fl_win / (pass_avg[2] * 1e-3) / 1e12
     if mfma_window:
         # the 16x16 Toeplitz blocks also multiply the zero upper triangle
-        pts = (cfg["nkx"] // 2 + 1) * (cfg["nky"] // 2 + 1)
+        pts = (cfg["nkx"] // 2 + 1) * (cfg["nky"] // 2 + 1) * window_half(cfg)
         passes["p3_window"]["mfma_issued_TFLOP/s"] = pts * 16 * 2 * 16 ** 3 / (pass_avg[2] * 1e-3) / 1e12
     if mfma4_window:
         # 4x4 rank-1 blocks, one point each: tile t of 16 lags takes 16 (t + 1)
         # steps, plus the zero-padded ends (T(T-1)/2 partial chunks per group skipped)
-        pts = (cfg["nkx"] // 2 + 1) * (cfg["nky"] // 2 + 1)
+        pts = (cfg["nkx"] // 2 + 1) * (cfg["nky"] // 2 + 1) * window_half(cfg)
         nT = (plan.info.lag_hi + 15) // 16
         steps4 = sum(16 * (t + 1) for t in range(nT))
         passes["p3_window"]["mfma_issued_TFLOP/s"] = pts * steps4 * 32 / (pass_avg[2] * 1e-3) / 1e12
