@@ -1216,8 +1216,9 @@ static lindhard_status build_plan_object(const lindhard_problem *p, lindhard_pla
     if (pl.p.want_rpa)
         LH_TRY(hipMemsetAsync(pl.im1, 0, (size_t)pl.g.neps * nk * pl.elem_bytes, st));
     if (pl.g.even) {
-        // the padding rows of the tiles (ry >= Hy) are carried through the
-        // window but never read back; keep them zero rather than stale
+        // the padding of the tiles (rows ry >= Hy, columns rx > nkx/2) is carried
+        // through the window, but the inverse passes take it as zero; keep it zero
+        // rather than stale
         const size_t sl = pl.g.slice_e * pl.elem_bytes;
         LH_TRY(hipMemsetAsync(pl.spec, 0, (size_t)pl.g.nslots * sl, st));
         if (pl.bspec) LH_TRY(hipMemsetAsync(pl.bspec, 0, (size_t)pl.nb * pl.g.nS * sl, st));
@@ -1266,7 +1267,7 @@ size_t plan_resident_bytes(lindhard_plan_t plan)
 // that are too small for the new geometry are replaced, and the window
 // schedule is taken from the tuning cache.  The result equals that of a plan
 // built for the problem afresh, bit for bit (the same geometry, schedule and
-// kernels; every buffer is written before it is read).  Synchronous on st;
+// kernels; every value a result depends on is written before it is read).  Synchronous on st;
 // the plan's earlier work must have completed.  EINVAL if the class differs.
 lindhard_status plan_rebind(lindhard_plan_t plan, const lindhard_problem *p, hipStream_t st)
 {
@@ -1307,7 +1308,7 @@ lindhard_status plan_rebind(lindhard_plan_t plan, const lindhard_problem *p, hip
     if (s != LINDHARD_OK) return s;
     LH_TRY(launch_tables(pl, st));
     if (pl.g.even) {
-        // replaced spectral buffers: padding rows zero, as at planning
+        // replaced spectral buffers: padding zero, as at planning
         const size_t sl = pl.g.slice_e * pl.elem_bytes;
         for (size_t i = 0; i < nb.size(); ++i)
             if (grown[i] && (nb[i].ptr == &pl.spec || nb[i].ptr == &pl.bspec || nb[i].ptr == &pl.sacc))

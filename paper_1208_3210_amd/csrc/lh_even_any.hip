@@ -246,7 +246,8 @@ __global__ void __launch_bounds__((ev_threads<T, LOGM>()), (sizeof(T) == 4 ? 6 :
 // a wave's loads and stores cover whole tile rows.  In place, one slice at a
 // time for sj slices, streamed past the L1, which holds the tables (2.96 -> 2.47
 // ms at 2049^2 x 512).  upper: only the rows ry >= Ce tile are stored (the forward
-// pass with the exchange symmetry).
+// pass with the exchange symmetry).  The padding columns (rx > nkx / 2) are taken as
+// zero (see ecol_body).
 template <typename T, int LOGM>
 __global__ void __launch_bounds__((ev_threads<T, LOGM>()), (sizeof(T) == 4 ? 6 : 3))
     k_becol(T *__restrict__ spec, Geo g, EvTab ty, int nslices, int sj, int upper)
@@ -260,7 +261,8 @@ __global__ void __launch_bounds__((ev_threads<T, LOGM>()), (sizeof(T) == 4 ? 6 :
     const int line = tid % L, q = tid / L;                 // first pass
     const int line2 = tid / F::TL, q2 = tid % F::TL;       // length-P transforms
     const int tile = blockIdx.x * (L / C) + line / C, c = line % C;
-    const bool act = q <= F::P / 2 && tile < g.NTe;
+    const int rx = tile * g.Ce + 2 * c;  // first column of the pair
+    const bool act = q <= F::P / 2 && tile < g.NTe && rx <= g.L;
     const int H = g.nky / 2, nlo = upper ? tile * g.Ce : 0;
     ev_fill_t2<T, LOGM>(t2, ty, tid);
     const int s0 = blockIdx.y * sj, s1 = min(nslices, s0 + sj);
@@ -273,7 +275,9 @@ __global__ void __launch_bounds__((ev_threads<T, LOGM>()), (sizeof(T) == 4 ? 6 :
         for (int i = 0; i < kNz; ++i) {
             const int n = ev_index<F::P>(i, qo);
             const bool in = act && n <= H;
-            x[i] = cmul(load_nt(at32(base, o0 + (in ? n : 0) * C)), ev_chirp<T>(ty, n, in));
+            cx<T> z0 = load_nt(at32(base, o0 + (in ? n : 0) * C));
+            if (rx + 1 > g.L) z0.y = (T)0;
+            x[i] = cmul(z0, ev_chirp<T>(ty, n, in));
         }
         ev_convolve<T, LOGM>(x, lds + line * LS, lds + line2 * LS, t2, ty, qo, act, q2 + z);
         if (act) {

@@ -227,7 +227,8 @@ __global__ void __launch_bounds__((se_threads<T, LOGN>()), (sizeof(T) == 4 ? kSe
 
 // P2 (INV false), P4 (INV true): each line is a pair of neighbouring real columns
 // of a tile (one complex value per row), the lines of a tile interleaved lane by
-// lane so that a wave's loads and stores cover whole tile rows.  In place.
+// lane so that a wave's loads and stores cover whole tile rows.  In place.  The inverse
+// takes the padding columns (rx > nkx/2) as zero (see ecol_body).
 template <typename T, int LOGN, bool INV, bool PAST = false>
 __device__ __forceinline__ void secol_body(T *__restrict__ spec, const Geo &g, const cx<T> *__restrict__ tab)
 {
@@ -241,17 +242,21 @@ __device__ __forceinline__ void secol_body(T *__restrict__ spec, const Geo &g, c
     const int line = tid % L, q = tid / L;            // first pass
     const int line2 = tid / F::TL, q2 = tid % F::TL;  // length-P transforms
     const int tile0 = blockIdx.x * (L / C), tile = tile0 + line / C, c = line % C;
-    const bool act = q <= F::P / 2 && tile < g.NTe;
+    const int rx = tile * g.Ce + 2 * c;  // first column of the pair
+    const bool in = tile < g.NTe && (!INV || rx <= g.L), act = q <= F::P / 2 && in;
     se_fill_t2<T, LOGN>(t2, tab, tid);
     cx<T> *base = reinterpret_cast<cx<T> *>(spec + (size_t)blockIdx.y * g.slice_e);
     const unsigned o0 = (unsigned)((act ? tile : 0) * g.HyS * C + c);
     cx<T> v[16];
     if (act) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = *at32(base, o0 + se_index<F::P>(i, q) * C);
+        for (int i = 0; i < 16; ++i) {
+            v[i] = *at32(base, o0 + se_index<F::P>(i, q) * C);
+            if (INV && rx + 1 > g.L) v[i].y = (T)0;
+        }
     }
     se_forward<T, LOGN>(v, lds + line * LS, lds + line2 * LS, t2, tab, q, act, q2);
-    if (q > 8 * F::R3 || tile >= g.NTe) return;
+    if (q > 8 * F::R3 || !in) return;
     // rows n = q + 8 R3 i (and n = N / 2), the lines side by side; with the
     // exchange symmetry the window reads the rows ry >= Ce tile only
     const int nlo = INV || !g.sw ? 0 : tile * g.Ce, i1 = q < 8 * F::R3 ? 16 : 1;

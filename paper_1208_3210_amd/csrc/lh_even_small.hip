@@ -180,6 +180,11 @@ __device__ __forceinline__ void small_inv(const T *__restrict__ spec, const Geo 
                 v[s] = mk<T>(wa * v[s].x + wb * y.x, wa * v[s].y + wb * y.y);
             }
         }
+        // (column H's partner is padding, which the half window does not write)
+        if (2 * ln + 1 > H) {
+#pragma unroll
+            for (int s = 0; s < E; ++s) v[s].y = (T)0;
+        }
         for (int i = tid; i < N; i += S::NT) l.tw[tw_swz(i)] = twx[i];
         __syncthreads();
         F::run(v, l.line + ln * N, l.tw, 0, gg, lds_xor_interleaved<T, N>(c, S::C));

@@ -782,6 +782,9 @@ __global__ void __launch_bounds__(kThreads, sizeof(T) == 4 ? 4 : 1) k_e1_batch(c
 // Column pass (even), forward or inverse: each line is a pair of adjacent
 // real columns of a tile (read as one complex value per row); rows above
 // nky/2 are the mirror of the stored ones.  Transformed in place.
+// The inverse takes the padding columns (rx > nkx/2) as zero: the half window
+// does not write all of their rows, and what an earlier call's inverse left there would
+// be transformed again beside column nkx/2, its partner, growing each time.
 template <typename T, int LOGN, bool INV>
 __device__ __forceinline__ void ecol_body(T *__restrict__ spec, const Geo &g,
                                                            const cx<T> *__restrict__ twy)
@@ -797,7 +800,8 @@ __device__ __forceinline__ void ecol_body(T *__restrict__ spec, const Geo &g,
     const int line = tid % NL, gg = tid / NL;
     const int tb = line / C, c = line % C;
     const int tile = blockIdx.x * TPB + tb;
-    const bool active = tile < g.NTe;
+    const int rx = tile * 2 * C + 2 * c;  // first column of the pair
+    const bool active = tile < g.NTe && (!INV || rx <= g.L);
     const int Hy = g.Hy;
     // twiddles first: the barrier that ends the copy then does not wait for
     // the column loads as well
@@ -810,6 +814,7 @@ __device__ __forceinline__ void ecol_body(T *__restrict__ spec, const Geo &g,
         const int ky = gg + s * G;
         const int row = ky <= N / 2 ? ky : N - ky;
         v[s] = active ? base[row * C + c] : mk<T>((T)0, (T)0);
+        if (INV && rx + 1 > g.L) v[s].y = (T)0;
     }
     F::run(v, lds + line * N, tw, 0, gg, lds_xor_interleaved<T, N>(line, NL));
     if (active) {
