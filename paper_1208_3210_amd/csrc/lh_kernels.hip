@@ -1388,7 +1388,9 @@ __global__ void __launch_bounds__(kThreads, 4) k_e3m(T *__restrict__ spec, Geo g
                 if (g.sw) {  // the exchanged points take the same values
 #pragma unroll
                     for (int i = 0; i < VEC; ++i) {
-                        const long pm = win_mirror(g, run.t, run.r + ((pq + i) >> g.logCe), (pq + i) & (g.Ce - 1));
+                        // (a run of four points may start in the middle of a tile row)
+                        const int e = (int)(p0 & (g.Ce - 1)) + pq + i;
+                        const long pm = win_mirror(g, run.t, run.r + (e >> g.logCe), e & (g.Ce - 1));
                         if (pm >= 0) spec[(size_t)(m - g.m_lo) * sl + pm] = tile[row * TS + pq + i];
                     }
                 }
