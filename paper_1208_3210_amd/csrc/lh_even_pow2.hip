@@ -250,9 +250,11 @@ __device__ __forceinline__ void secol_body(T *__restrict__ spec, const Geo &g, c
     cx<T> v[16];
     if (act) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            v[i] = *at32(base, o0 + se_index<F::P>(i, q) * C);
-            if (INV && rx + 1 > g.L) v[i].y = (T)0;
+        for (int i = 0; i < 16; ++i) v[i] = *at32(base, o0 + se_index<F::P>(i, q) * C);
+        // (a branch of the last block only: on every path it takes registers)
+        if (INV && tile0 + L / C >= g.NTe) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i].y = rx + 1 > g.L ? (T)0 : v[i].y;
         }
     }
     se_forward<T, LOGN>(v, lds + line * LS, lds + line2 * LS, t2, tab, q, act, q2);

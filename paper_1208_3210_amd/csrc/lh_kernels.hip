@@ -814,7 +814,11 @@ __device__ __forceinline__ void ecol_body(T *__restrict__ spec, const Geo &g,
         const int ky = gg + s * G;
         const int row = ky <= N / 2 ? ky : N - ky;
         v[s] = active ? base[row * C + c] : mk<T>((T)0, (T)0);
-        if (INV && rx + 1 > g.L) v[s].y = (T)0;
+    }
+    // (a branch of the last block only: on every path it takes registers)
+    if (INV && (int)(blockIdx.x + 1) * TPB >= g.NTe) {
+#pragma unroll
+        for (int s = 0; s < E; ++s) v[s].y = rx + 1 > g.L ? (T)0 : v[s].y;
     }
     F::run(v, lds + line * N, tw, 0, gg, lds_xor_interleaved<T, N>(line, NL));
     if (active) {
