@@ -857,9 +857,11 @@ __global__ void __launch_bounds__(col_threads(LOGN)) k_ecol_batch(const EvenInst
 // blocks of 16 lags held in registers with a 16-value sliding window of H'
 // (16 FMAs per two LDS reads).  Products are summed in T over 32 steps; the
 // block sums are accumulated in FP64 (compensating the FP32 partial sums) and
-// the lane partials are merged in FP64.  COMP selects nothing else today: the
-// FP64 instantiation sums in FP64 throughout.
-template <typename T, bool COMP, int TR>
+// the lane partials are merged in FP64 (FP64 sums in FP64 throughout).
+// SW: the exchange symmetry.  A kernel of its own: the place of a run and its mirror
+// take registers, and with them in the one on all points FP64 at 64 points per block
+// took 169 (two waves per SIMD, not three; one lag at 2048 x 256: 29 us against 22).
+template <typename T, int TR, bool SW>
 __device__ __forceinline__ void e3_body(T *__restrict__ spec, const Geo &g)
 {
     constexpr int SU = 64 / TR;
@@ -870,9 +872,10 @@ __device__ __forceinline__ void e3_body(T *__restrict__ spec, const Geo &g)
     T *Pz = lds;                    // [PL][TR]
     T *Hz = lds + (size_t)PL * TR;  // [HP + HL][TR], row (HP + x)
     const int tid = threadIdx.x;
+    const size_t p0 = (size_t)xcd_tile(blockIdx.x, gridDim.x) * TR, np = SW ? win_points(g) : g.slice_e;
     // this thread's point (the same in every staging step: TR divides the block)
-    const size_t pi = (size_t)xcd_tile(blockIdx.x, gridDim.x) * TR + tid % TR, np = win_points(g);
-    const WinRun run = win_run(g, pi < np ? pi : 0);
+    const size_t pi = p0 + tid % TR;
+    const WinRun run = SW ? win_run(g, pi < np ? pi : 0) : WinRun{pi, 0, 0};
     const size_t pt = run.p;
     const int ne = g.nS, j0 = g.j0 - g.jA;
     const size_t sl = g.slice_e;
@@ -971,32 +974,35 @@ __device__ __forceinline__ void e3_body(T *__restrict__ spec, const Geo &g)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[i] += __shfl_xor(acc[i], o, 64);
         }
-        if (su == 0 && pi < np) {
-            const long pm = win_mirror(g, run.t, run.r, (int)(pt & (g.Ce - 1)));
+        if (su == 0 && p0 + p < np) {
+            const size_t po = SW ? pt : p0 + p;
+            const long pm = SW ? win_mirror(g, run.t, run.r, (int)(pt & (g.Ce - 1))) : -1;
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const int m = mf + i;
                 if (m > g.m_hi) break;
                 T *dst = spec + (size_t)(m - g.m_lo) * sl;
-                dst[pt] = (T)acc[i];
-                if (pm >= 0) dst[pm] = (T)acc[i];
+                dst[po] = (T)acc[i];
+                if (SW && pm >= 0) dst[pm] = (T)acc[i];
             }
         }
     }
 }
 
-template <typename T, bool COMP, int TR>
-__global__ void __launch_bounds__(kThreads) k_e3(T *__restrict__ spec, Geo g)
+template <typename T, int TR>
+constexpr int e3_waves() { return sizeof(T) == 8 && TR == 64 ? 3 : 1; }
+template <typename T, int TR, bool SW>
+__global__ void __launch_bounds__(kThreads, (e3_waves<T, TR>())) k_e3(T *__restrict__ spec, Geo g)
 {
-    e3_body<T, COMP, TR>(spec, g);
+    e3_body<T, TR, SW>(spec, g);
 }
 // Batched direct window: instance blockIdx.z
-template <typename T, bool COMP, int TR>
-__global__ void __launch_bounds__(kThreads) k_e3_batch(const EvenInst *__restrict__ in)
+template <typename T, int TR, bool SW>
+__global__ void __launch_bounds__(kThreads, (e3_waves<T, TR>())) k_e3_batch(const EvenInst *__restrict__ in)
 {
     const EvenInst &d = in[blockIdx.z];
     const Geo g = d.g;
-    e3_body<T, COMP, TR>((T *)d.spec, g);
+    e3_body<T, TR, SW>((T *)d.spec, g);
 }
 
 // Energy window (even) on the matrix cores.  The same convolution
@@ -1240,7 +1246,9 @@ __device__ __forceinline__ T e3m_gload(const T *col, bool pv, const E3mStageS &s
     return ok ? xv : (T)0;
 }
 
-template <typename T, int TR>
+// SW: the exchange symmetry (a kernel of its own: the mirrored stores take registers, and
+// spilled 45 of 128 in FP32 at 16 points per block against 2 without them).
+template <typename T, int TR, bool SW>
 __global__ void __launch_bounds__(kThreads, 4) k_e3m(T *__restrict__ spec, Geo g, int ntiles)
 {
     static_assert(TR >= 4 && (TR & (TR - 1)) == 0, "TR: power of two >= 4");
@@ -1254,6 +1262,8 @@ __global__ void __launch_bounds__(kThreads, 4) k_e3m(T *__restrict__ spec, Geo g
     const int tid = threadIdx.x;
     const int j0 = g.j0 - g.jA;
     const size_t sl = g.slice_e;
+    // first point of tile t
+    auto place = [&](int t) { return SW ? win_run(g, (size_t)t * TR) : WinRun{(size_t)t * TR, 0, 0}; };
     // Persistent blocks: the blocks of one XCD (launch index mod 8) walk one
     // contiguous range of tiles, so neighbouring tiles meet in that XCD's L2.
     const int xcd = blockIdx.x & 7, bi = blockIdx.x >> 3, bx = gridDim.x >> 3;
@@ -1311,22 +1321,22 @@ __global__ void __launch_bounds__(kThreads, 4) k_e3m(T *__restrict__ spec, Geo g
     T *tile = overlay ? lds : lds + (size_t)TR * PS;
 
     if (prefetch) {
-        const E3mRsrc rs = e3m_rsrc(spec, sl, j0, nA, nHe, win_run(g, (size_t)t * TR).p);
+        const E3mRsrc rs = e3m_rsrc(spec, sl, j0, nA, nHe, place(t).p);
 #pragma unroll
         for (int k = 0; k < NPF; ++k) pf[k] = e3m_bload<T>(rs, st, r0 + k * RP);
 #pragma unroll
         for (int k = 0; k < NPF; ++k) e3m_put<T>(lds, PS, q * VEC, rows, r0 + k * RP, pf[k]);
     } else {
-        stage_sync(win_run(g, (size_t)t * TR).p);
+        stage_sync(place(t).p);
     }
     __syncthreads();
     for (;;) {
-        const WinRun run = win_run(g, (size_t)t * TR);
+        const WinRun run = place(t);
         const size_t p0 = run.p;
         const int tn = t + bx;
         const bool more = tn < t_end;
         if (prefetch && more) {  // in flight during the products
-            const E3mRsrc rs = e3m_rsrc(spec, sl, j0, nA, nHe, win_run(g, (size_t)tn * TR).p);
+            const E3mRsrc rs = e3m_rsrc(spec, sl, j0, nA, nHe, place(tn).p);
             // The row offsets do not change from tile to tile; hiding r0 from
             // the optimiser keeps it from holding all NPF of them in registers
             // for the whole kernel (they are cheap to recompute).
@@ -1389,7 +1399,7 @@ __global__ void __launch_bounds__(kThreads, 4) k_e3m(T *__restrict__ spec, Geo g
                     for (int i = 0; i < VEC; ++i)
                         if (pb + i < sl) dst[i] = tile[row * TS + pq + i];
                 }
-                if (g.sw) {  // the exchanged points take the same values
+                if constexpr (SW) {  // the exchanged points take the same values
 #pragma unroll
                     for (int i = 0; i < VEC; ++i) {
                         // (a run of four points may start in the middle of a tile row)
@@ -1407,7 +1417,7 @@ __global__ void __launch_bounds__(kThreads, 4) k_e3m(T *__restrict__ spec, Geo g
 #pragma unroll
             for (int k = 0; k < NPF; ++k) e3m_put<T>(lds, PS, q * VEC, rows, r0 + k * RP, pf[k]);
         } else
-            stage_sync(win_run(g, (size_t)t * TR).p);
+            stage_sync(place(t).p);
         __syncthreads();
     }
 }
@@ -2778,8 +2788,8 @@ static hipError_t exec_t(const Plan &pl, T *out, hipStream_t st, hipEvent_t *ev)
 
 // Persistent launch of the matrix-core window: as many blocks as fit on the
 // device at once (a multiple of 8, one share per XCD), each walking tiles.
-template <typename T, int TR>
-static hipError_t launch_e3m(const Plan &pl, T *spr, int ntiles, size_t lds, hipStream_t st)
+template <typename T, int TR, bool SW>
+static hipError_t launch_e3m_sw(const Plan &pl, T *spr, int ntiles, size_t lds, hipStream_t st)
 {
     static std::mutex mu;
     static std::map<std::pair<int, size_t>, int> fit;  // (device, LDS bytes) -> blocks per CU
@@ -2791,7 +2801,7 @@ static hipError_t launch_e3m(const Plan &pl, T *spr, int ntiles, size_t lds, hip
             per_cu = it->second;
         } else {
             LH_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &per_cu, reinterpret_cast<const void *>(&k_e3m<T, TR>), kThreads, lds));
+                &per_cu, reinterpret_cast<const void *>(&k_e3m<T, TR, SW>), kThreads, lds));
             per_cu = std::max(1, per_cu);
             fit[{pl.device, lds}] = per_cu;
         }
@@ -2800,8 +2810,14 @@ static hipError_t launch_e3m(const Plan &pl, T *spr, int ntiles, size_t lds, hip
     LH_HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, pl.device));
     const long want = ((long)ntiles + 7) / 8 * 8;
     const int blocks = (int)std::max(8L, std::min(want, (long)ncu * per_cu / 8 * 8));
-    hipLaunchKernelGGL((k_e3m<T, TR>), dim3(blocks), dim3(kThreads), lds, st, spr, pl.g, ntiles);
+    hipLaunchKernelGGL((k_e3m<T, TR, SW>), dim3(blocks), dim3(kThreads), lds, st, spr, pl.g, ntiles);
     return hipGetLastError();
+}
+template <typename T, int TR>
+static hipError_t launch_e3m(const Plan &pl, T *spr, int ntiles, size_t lds, hipStream_t st)
+{
+    return pl.g.sw ? launch_e3m_sw<T, TR, true>(pl, spr, ntiles, lds, st)
+                   : launch_e3m_sw<T, TR, false>(pl, spr, ntiles, lds, st);
 }
 
 // The energy-window pass alone (autotuner timing).
@@ -2819,10 +2835,8 @@ static hipError_t window_t(const Plan &pl, hipStream_t st)
         const dim3 g3(cdiv(win_points(g), g.e3_TR));
 #define LH_E3(TRV)                                                                                    \
     do {                                                                                              \
-        if (g.fp64)                                                                                   \
-            hipLaunchKernelGGL((k_e3<T, false, TRV>), g3, dim3(kThreads), lds3, st, spr, g);          \
-        else                                                                                          \
-            hipLaunchKernelGGL((k_e3<T, true, TRV>), g3, dim3(kThreads), lds3, st, spr, g);           \
+        const auto k = g.sw ? &k_e3<T, TRV, true> : &k_e3<T, TRV, false>;                             \
+        hipLaunchKernelGGL(k, g3, dim3(kThreads), lds3, st, spr, g);                                  \
     } while (0)
         if (g.e3_variant == 2) {
             if constexpr (sizeof(T) == 4) return launch_e3q(pl, g.e3q_W, st);
@@ -2975,10 +2989,8 @@ static hipError_t even_group_t(const Plan *const *pls, int n, const EvenInst *d,
         const dim3 g3(cdiv(win_points(g), g.e3_TR), 1, nz);
 #define LH_E3B(TRV)                                                                                                 \
     do {                                                                                                            \
-        if (g.fp64)                                                                                                 \
-            hipLaunchKernelGGL((k_e3_batch<T, false, TRV>), g3, dim3(kThreads), lds3, st, d);                       \
-        else                                                                                                        \
-            hipLaunchKernelGGL((k_e3_batch<T, true, TRV>), g3, dim3(kThreads), lds3, st, d);                        \
+        const auto k = g.sw ? &k_e3_batch<T, TRV, true> : &k_e3_batch<T, TRV, false>;                               \
+        hipLaunchKernelGGL(k, g3, dim3(kThreads), lds3, st, d);                                                     \
     } while (0)
         switch (g.e3_TR) {
         case 64: LH_E3B(64); break;

@@ -129,7 +129,9 @@ struct MixArgs {
 // BIG: the staged slice ranges or the output reach past 4 GiB of byte
 // offsets, so the block uses 64-bit addresses (flat loads and stores) instead
 // of buffer descriptors.
-template <bool BIG, bool MIX = false>
+// SW: the exchange symmetry (without it no place or mirror is worked out: 2048 x 256
+// points x 64 lags 42.5 -> 40 us).
+template <bool BIG, bool SW, bool MIX = false>
 __device__ __forceinline__ void e3q_body(float *__restrict__ spec, const Geo &g, const MixArgs *mx = nullptr)
 {
     static_assert(!(BIG && MIX), "mixed bands: 32-bit offsets");
@@ -140,7 +142,8 @@ __device__ __forceinline__ void e3q_body(float *__restrict__ spec, const Geo &g,
     const int tid = threadIdx.x;
     const size_t sl = g.slice_e;
     const unsigned sl4 = (unsigned)(sl * 4);
-    const WinRun run = win_run(g, (size_t)xcd_block(blockIdx.x, gridDim.x) * kPoints);
+    const size_t i0 = (size_t)xcd_block(blockIdx.x, gridDim.x) * kPoints;
+    const WinRun run = SW ? win_run(g, i0) : WinRun{i0, 0, 0};
     const size_t p0 = run.p;
     const int j0r = g.j0 - g.jA;
     const int nAst = g.e3q_nAst, nHst = g.e3q_nHst;
@@ -248,7 +251,7 @@ __device__ __forceinline__ void e3q_body(float *__restrict__ spec, const Geo &g,
         __builtin_amdgcn_make_buffer_rsrc((void *)(MIX ? mx->out : spec), 0, (int)((size_t)nL * sl * 4), 0x00020000);
     const unsigned ob0 = (unsigned)((p0 + b) * 4) + (unsigned)(4 * qd) * sl4;
     // the exchanged point (rx, ry swapped) takes the same values
-    const long pm = win_mirror(g, run.t, run.r + (b >> g.logCe), b & (g.Ce - 1));
+    const long pm = SW ? win_mirror(g, run.t, run.r + (b >> g.logCe), b & (g.Ce - 1)) : -1;
     const unsigned obm = (unsigned)(pm * 4) + (unsigned)(4 * qd) * sl4;
 
     for (int gi = 0; gi < G; ++gi) {
@@ -352,13 +355,13 @@ __device__ __forceinline__ void e3q_body(float *__restrict__ spec, const Geo &g,
                     const unsigned os = (unsigned)(16 * t + i) * sl4;
                     if constexpr (BIG) {
                         spec[(size_t)slot * sl + p0 + b] = v;
-                        if (pm >= 0) spec[(size_t)slot * sl + pm] = v;
+                        if (SW && pm >= 0) spec[(size_t)slot * sl + pm] = v;
                     } else {
                         if constexpr (MIX)
                             if (mx->acc)
                                 v += __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rO, (int)(ob0 + os), 0, 0));
                         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rO, (int)(ob0 + os), 0, 0);
-                        if (pm >= 0)
+                        if (SW && pm >= 0)
                             __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rO, (int)(obm + os), 0, 0);
                     }
                 }
@@ -367,22 +370,23 @@ __device__ __forceinline__ void e3q_body(float *__restrict__ spec, const Geo &g,
     }
 }
 
-template <bool BIG>
+template <bool BIG, bool SW>
 __global__ void __launch_bounds__(64 * kWaves) k_e3q(float *__restrict__ spec, Geo g)
 {
-    e3q_body<BIG>(spec, g);
+    e3q_body<BIG, SW>(spec, g);
 }
+template <bool SW>
 __global__ void __launch_bounds__(64 * kWaves) k_e3q_mix(Geo g, MixArgs mx)
 {
-    e3q_body<false, true>(nullptr, g, &mx);
+    e3q_body<false, SW, true>(nullptr, g, &mx);
 }
 // Batched form: instance blockIdx.z of the descriptors
-template <bool BIG>
+template <bool BIG, bool SW>
 __global__ void __launch_bounds__(64 * kWaves) k_e3q_batch(const EvenInst *__restrict__ in)
 {
     const EvenInst &d = in[blockIdx.z];
     const Geo g = d.g;
-    e3q_body<BIG>((float *)d.spec, g);
+    e3q_body<BIG, SW>((float *)d.spec, g);
 }
 
 }  // namespace
@@ -397,10 +401,9 @@ hipError_t launch_e3q(const Plan &pl, int, hipStream_t st)
 {
     const Geo &g = pl.g;
     const dim3 grid((unsigned)((win_points(g) + kPoints - 1) / kPoints));
-    if (g.e3q_big)
-        hipLaunchKernelGGL(k_e3q<true>, grid, dim3(64 * kWaves), e3q_lds_bytes(g, 1), st, (float *)pl.spec, g);
-    else
-        hipLaunchKernelGGL(k_e3q<false>, grid, dim3(64 * kWaves), e3q_lds_bytes(g, 1), st, (float *)pl.spec, g);
+    const auto k = g.e3q_big ? (g.sw ? &k_e3q<true, true> : &k_e3q<true, false>)
+                             : (g.sw ? &k_e3q<false, true> : &k_e3q<false, false>);
+    hipLaunchKernelGGL(k, grid, dim3(64 * kWaves), e3q_lds_bytes(g, 1), st, (float *)pl.spec, g);
     return hipGetLastError();
 }
 
@@ -426,7 +429,8 @@ hipError_t launch_e3q_mix(const Plan &pl, int nu, const double *w, void *out, bo
     mx.out = (float *)out;
     mx.acc = acc ? 1 : 0;
     const dim3 grid((unsigned)((win_points(g) + kPoints - 1) / kPoints));
-    hipLaunchKernelGGL(k_e3q_mix, grid, dim3(64 * kWaves), e3q_lds_bytes(g, 1), st, g, mx);
+    const auto k = g.sw ? &k_e3q_mix<true> : &k_e3q_mix<false>;
+    hipLaunchKernelGGL(k, grid, dim3(64 * kWaves), e3q_lds_bytes(g, 1), st, g, mx);
     return hipGetLastError();
 }
 
@@ -441,10 +445,10 @@ hipError_t launch_e3q_group(const Plan *const *pls, int n, const EvenInst *d_des
         big = big || pls[i]->g.e3q_big;
     }
     const dim3 grid((unsigned)((win_points(pls[0]->g) + kPoints - 1) / kPoints), 1, (unsigned)n);
-    if (big)
-        hipLaunchKernelGGL(k_e3q_batch<true>, grid, dim3(64 * kWaves), lds, st, d_desc);
-    else
-        hipLaunchKernelGGL(k_e3q_batch<false>, grid, dim3(64 * kWaves), lds, st, d_desc);
+    const bool sw = pls[0]->g.sw != 0;  // (equal in a group)
+    const auto k = big ? (sw ? &k_e3q_batch<true, true> : &k_e3q_batch<true, false>)
+                       : (sw ? &k_e3q_batch<false, true> : &k_e3q_batch<false, false>);
+    hipLaunchKernelGGL(k, grid, dim3(64 * kWaves), lds, st, d_desc);
     return hipGetLastError();
 }
 
