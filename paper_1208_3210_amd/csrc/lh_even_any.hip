@@ -296,7 +296,8 @@ __global__ void __launch_bounds__((ev_threads<T, LOGM>()), (sizeof(T) == 4 ? 6 :
 // 16-byte pieces.  The result rows C(qx), qx = 0 .. H, are the output rows qy and
 // nky - qy at columns qx and nkx - qx, scaled and written Gamma-centred into
 // every zone image, times the orbital |M(Q)|^2 if ff (MODE 0); MODE 1 (the RPA
-// path) writes the first-zone map of window slot `plane`.
+// path) writes the first-zone map of window slot `plane`.  blockIdx.z: the block's
+// share of the zone images (see pass_t).
 template <typename T, int LOGM, int MODE>
 __global__ void __launch_bounds__((ev_threads<T, LOGM>()), (sizeof(T) == 4 ? 6 : 3))
     k_be5(const T *__restrict__ spec, Geo g, EvTab tx, const PlaneSrc *__restrict__ psrc, double scale,
@@ -314,16 +315,20 @@ __global__ void __launch_bounds__((ev_threads<T, LOGM>()), (sizeof(T) == 4 ? 6 :
     const int plane = blockIdx.y, row0 = blockIdx.x * 2 * L;
     const PlaneSrc ps = MODE == 0 ? psrc[plane] : PlaneSrc{plane, -1, 1.0, 0.0};
     const int onx = MODE == 0 ? zx * nkx : nkx, ony = MODE == 0 ? zy * nky : nky;
-    const int nzx = MODE == 0 ? zx : 1, nzy = MODE == 0 ? zy : 1;
+    // zone images [im0, im1) of nzx columns of images
+    const int nzx = MODE == 0 ? zx : 1, nim = MODE == 0 ? zx * zy : 1;
+    const int per = (nim + (int)gridDim.z - 1) / (int)gridDim.z;
+    const int im0 = (int)blockIdx.z * per, im1 = min(nim, im0 + per);
     const int sx = MODE == 0 ? (zx * nkx) / 2 % nkx : 0, sy = MODE == 0 ? (zy * nky) / 2 % nky : 0;
     const size_t oplane = (size_t)(MODE == 0 ? plane : g.m_lo + plane) * ony;
     if (MODE == 0 && ps.a < 0) {  // the plane is zero (block-uniform)
         for (int r = 0; r < 2 * L && row0 + r < Hy; ++r)
             for (int mir = 0; mir < 2; ++mir) {
                 const int qy = mir ? (nky - (row0 + r)) % nky : row0 + r;
-                for (int zi = 0; zi < nzy; ++zi) {
-                    T *orow = out + (oplane + zi * nky + (qy + sy) % nky) * onx;
-                    for (int X = tid; X < onx; X += NT) orow[X] = (T)0;
+                for (int im = im0; im < im1; ++im) {
+                    const int zi = im / nzx, zj = im - zi * nzx;
+                    T *orow = out + (oplane + zi * nky + (qy + sy) % nky) * onx + (size_t)zj * nkx;
+                    for (int X = tid; X < nkx; X += NT) orow[X] = (T)0;
                 }
             }
         return;
@@ -369,29 +374,26 @@ __global__ void __launch_bounds__((ev_threads<T, LOGM>()), (sizeof(T) == 4 ? 6 :
             const int qy = mir ? (nky - qy0) % nky : qy0;
             if (mir && qy == qy0) continue;
             const int yv = (qy + sy) % nky;
-            for (int zi = 0; zi < nzy; ++zi) {
-                const int Y = zi * nky + yv;
+            for (int im = im0; im < im1; ++im) {
+                const int zi = im / nzx, zj = im - zi * nzx, Y = zi * nky + yv;
                 T *orow = out + (oplane + Y) * onx;
                 const double2 fy = MODE == 0 && ff ? ffy[Y] : make_double2(1.0, 0.0);
-                for (int zj = 0; zj < nzx; ++zj) {
-                    const int qo = q + opaque_zero();
+                const int qo = q + opaque_zero();
 #pragma unroll
-                    for (int i = 0; i < kNz; ++i) {
-                        const int n = ev_index<F::P>(i, qo);
-                        if (n > H) continue;
-                        const T val = (half ? x[i].y : x[i].x) * sc;
-                        // columns n and nkx - n (the same point when 2 n = 0 or nkx)
-                        const int Xa = n + sx, Xb = nkx - n + sx;
-                        const int xa = zj * nkx + (Xa >= nkx ? Xa - nkx : Xa);
-                        const int xb = zj * nkx + (Xb >= nkx ? Xb - nkx : Xb);
-                        if (MODE == 0 && ff) {
-                            orow[xa] = (T)((double)val * form_factor_sq(ffx[xa], fy, ffs));
-                            if (n > 0 && 2 * n != nkx)
-                                orow[xb] = (T)((double)val * form_factor_sq(ffx[xb], fy, ffs));
-                        } else {
-                            orow[xa] = val;
-                            if (n > 0 && 2 * n != nkx) orow[xb] = val;
-                        }
+                for (int i = 0; i < kNz; ++i) {
+                    const int n = ev_index<F::P>(i, qo);
+                    if (n > H) continue;
+                    const T val = (half ? x[i].y : x[i].x) * sc;
+                    // columns n and nkx - n (the same point when 2 n = 0 or nkx)
+                    const int Xa = n + sx, Xb = nkx - n + sx;
+                    const int xa = zj * nkx + (Xa >= nkx ? Xa - nkx : Xa);
+                    const int xb = zj * nkx + (Xb >= nkx ? Xb - nkx : Xb);
+                    if (MODE == 0 && ff) {
+                        orow[xa] = (T)((double)val * form_factor_sq(ffx[xa], fy, ffs));
+                        if (n > 0 && 2 * n != nkx) orow[xb] = (T)((double)val * form_factor_sq(ffx[xb], fy, ffs));
+                    } else {
+                        orow[xa] = val;
+                        if (n > 0 && 2 * n != nkx) orow[xb] = val;
                     }
                 }
             }
@@ -452,6 +454,15 @@ hipError_t pass_t(const Plan &pl, int pass, void *out, hipStream_t st)
 #undef LH_BEC
     } else {
         const int ff = pl.p.ff_kind != LINDHARD_FF_NONE;
+        // a block writes the zone images of its rows one after another (5 to 15 us each,
+        // the transform 10): they are dealt out to blocks that repeat the transform, up to
+        // 2048 blocks.  257^2 with the orbital, FP32, us a call: 5 x 5 zones x 1 omega 430 ->
+        // 67, x 50 omegas 452 -> 246 (with 512 blocks 289, 8192 279); 9 x 9 x 50
+        // 1585 -> 643 (889, 598), FP64 1977 -> 1536 (1886, 1478)
+        auto images = [&](unsigned nx) {
+            const long want = 2048 / std::max(1L, (long)nx * pl.p.nomega);
+            return (unsigned)std::max(1L, std::min({want, (long)pl.zx * pl.zy, 65535L}));
+        };
 #define LH_BE5(LG)                                                                                                   \
     do {                                                                                                             \
         constexpr int L = ev_lines<T, LG>();                                                                         \
@@ -461,7 +472,7 @@ hipError_t pass_t(const Plan &pl, int pass, void *out, hipStream_t st)
                                spec, g, ev_tab(pl, false), pl.d_src, pl.scale, (T *)pl.im1, 1, 1, 0, 0.0, pl.ffx,    \
                                pl.ffy);                                                                              \
         else                                                                                                         \
-            hipLaunchKernelGGL((k_be5<T, LG, 0>), dim3(nx, pl.p.nomega), dim3(ev_threads<T, LG>()),                  \
+            hipLaunchKernelGGL((k_be5<T, LG, 0>), dim3(nx, pl.p.nomega, images(nx)), dim3(ev_threads<T, LG>()),      \
                                (ev_lds<T, LG>(false)), st, spec, g, ev_tab(pl, false), pl.d_src, pl.scale, (T *)out, \
                                pl.zx, pl.zy, ff, pl.ff_s, pl.ffx, pl.ffy);                                           \
     } while (0)
