@@ -34,7 +34,7 @@ struct MapArgs {
     int ff, kzn;
     double ffs, V;
     const double2 *ffx, *ffy;
-    int logtx, nseg, wb;
+    int logtx, nseg, wb, zc;
 };
 
 // VEC consecutive values: one 16-byte access (or one element).
@@ -82,12 +82,12 @@ __global__ void __launch_bounds__(256) k_map(const T *__restrict__ im1, const T 
     const int u = (xu + a.nkx - ((a.zx * a.nkx) / 2) % a.nkx) % a.nkx;
     const size_t nk = (size_t)a.nkx * a.nky * a.nkz, q = ((size_t)vz * a.nky + vy) * a.nkx + u;
     const size_t plane = (size_t)a.out_nx * a.out_ny;
-    const int zj0 = (int)blockIdx.z * ZC;
+    const int zj0 = (int)blockIdx.z * a.zc, nz = min(a.zc, a.zx - zj0);  // (nz <= ZC)
     double m2[ZC][VEC], U[ZC][VEC];
     bool qz[ZC][VEC];
 #pragma unroll
     for (int z = 0; z < ZC; ++z) {
-        if (zj0 + z >= a.zx) break;
+        if (z >= nz) break;
 #pragma unroll
         for (int i = 0; i < VEC; ++i) {
             const int X = (zj0 + z) * a.nkx + xu + i;
@@ -139,7 +139,7 @@ __global__ void __launch_bounds__(256) k_map(const T *__restrict__ im1, const T 
         }
 #pragma unroll
         for (int z = 0; z < ZC; ++z) {
-            if (zj0 + z >= a.zx) break;
+            if (z >= nz) break;
             MV oi, orr, x = im, r = re;
 #pragma unroll
             for (int i = 0; i < VEC; ++i) {
@@ -198,8 +198,16 @@ hipError_t map_t(const Plan &pl, bool rpa, T *im, int vkind, double V, T *re, T 
     a.logtx = 4;
     while (a.logtx < 8 && (1 << a.logtx) < items) ++a.logtx;
     a.nseg = (items + (1 << a.logtx) - 1) >> a.logtx;
-    const int rpb = 256 >> a.logtx, zc = pl.zx == 1 ? 1 : pl.zx == 3 ? 3 : 5;
-    const int nblk = (g.nky * g.nkz + rpb - 1) / rpb * a.nseg * pl.zy, nz = (pl.zx + zc - 1) / zc;
+    // columns of zones in equal groups of up to five; of three while a block goes over
+    // at most eight omegas, too few to repay five zones' form factors and registers
+    // (a call with RPA, us: 256^2 x 5 x 5 zones x 8 omegas 105 -> 99, 512^2 x 9 x 9 x 1
+    // 215 -> 211, x 2 273 -> 267; at 60 omegas 256^2 x 5 x 5 takes 364 with five, 371 with
+    // three.  With 11 zones in 5 + 5 + 1: 512^2 x 2 346, in 4 + 4 + 3 336)
+    const int gmax = a.nw <= 8 ? 3 : 5;
+    const int rpb = 256 >> a.logtx, nz = (pl.zx + gmax - 1) / gmax;
+    a.zc = (pl.zx + nz - 1) / nz;
+    const int zc = a.zc == 1 ? 1 : a.zc <= 3 ? 3 : 5;
+    const int nblk = (g.nky * g.nkz + rpb - 1) / rpb * a.nseg * pl.zy;
     // omegas per block: 16 for one array and 8 for three (each measured best at
     // 128 omegas: 16 gives 0.61 / 1.89 ms, 8 gives 0.66 / 1.84), fewer while that
     // leaves less than two blocks per CU
