@@ -556,7 +556,7 @@ std::vector<BufSpec> plan_buffers(const Plan &cpl)
         {&pl.bspec, band_ws ? (size_t)pl.nb * g.nS * sl : 0},
         {&pl.sacc, pair_ws ? (size_t)g.nL * sl : 0},
         {&pl.twx, g.nkx * cs},
-        {&pl.twy, se_cols(g) ? 0 : g.nky * cs},
+        {&pl.twy, g.nky * cs},
         {&pl.twz, g.nkz > 1 ? g.nkz * cs : 0},
         {&pl.bsx[0], g.bs ? g.nkx * cs : 0},
         {&pl.bsy[0], g.bs ? g.nky * cs : 0},
@@ -579,8 +579,8 @@ std::vector<BufSpec> plan_buffers(const Plan &cpl)
         {(void **)&pl.kkw, rpa ? (size_t)pl.kk_ntiles * 16 * pl.kk_nch * 16 * 8 : 0},
         {(void **)&pl.d_kkrow, rpa ? pl.kk_rows.size() * sizeof(int2) : 0},
         {(void **)&pl.d_kkslot, rpa ? pl.kk_slot.size() * sizeof(int) : 0},
-        {&pl.evx, se_rows(g) ? even_any_twiddle_len(g.logNx) * cs : 0},
-        {&pl.evy, se_cols(g) ? even_any_twiddle_len(g.logNy) * cs : 0},
+        {&pl.evx, se_axis_x(g) ? even_any_twiddle_len(g.logNx) * cs : 0},
+        {&pl.evy, se_axis_y(g) ? even_any_twiddle_len(g.logNy) * cs : 0},
         {&pl.m2, pl.has_m2 ? (size_t)pl.nb * pl.nb * pl.out_nx * pl.out_ny * es : 0},
     };
 }

@@ -1,5 +1,5 @@
 // lh_even_pow2.hip -- builder and column passes of the even path on the half-work
-// transform (EvenFFT): axes of 1024 to 4096 points (FP64 columns from 512).
+// transform (EvenFFT): axes of 1024 to 4096 points (FP64 columns from 2048; se_rows, se_cols).
 //
 // Both have the butterfly's inputs computed or loaded by the thread that runs it
 // (each value once: the mirror images are never evaluated or read) and leave
@@ -7,12 +7,9 @@
 // 2048^2 x 512 x 256, ms: builder 0.86 -> 0.63, P2 0.90 -> 0.80, P4 0.47 -> 0.46 in
 // FP32, 2.00 -> 1.43, 1.76 -> 1.47 and 0.95 -> 0.87 in FP64; at 4096^2, FP32, 4.5 ->
 // 2.7, 4.8 -> 3.1 and 2.8 -> 1.8; at 1024^2, FP32, 0.26 -> 0.16, 0.24 -> 0.18 and 0.13 ->
-// 0.10.  At 512 points a block holds 16 rows and the two are equal in FP32 (P1
-// 24.2 and 24.7 us at 256 energies, P2 58.7 and 58.1 at 512), so the line lies
-// there; below, the full transforms' smaller blocks are faster (256^2 x 512: P1
-// 26.8 against 30.6 us).  The builder is bound by the vector units (73 % busy), the
-// columns by HBM.  The last row pass on the same transform (mirrored stores from
-// the butterflies) took 1.8 ms against 1.0 and is not kept.
+// 0.10.  The builder is bound by the vector units (73 % busy), the columns by HBM.  The
+// last row pass on the same transform (mirrored stores from the butterflies) took 1.8 ms
+// against 1.0 and is not kept.
 #include <algorithm>
 
 #include "lh_device.h"
@@ -82,14 +79,6 @@ __device__ __forceinline__ int se_index(int s, int g)
 {
     return s < 8 ? g + P * s : (16 - s) * P - g;
 }
-// Frequency of value i of thread (k, t) of the length-P transforms, and whether
-// it is stored: rows k = 0 and 8 hold every frequency twice.
-template <typename F>
-__device__ __forceinline__ int se_freq(int i, int k, int t)
-{
-    return k + 16 * (t + F::R3 * (i / F::R3) + 16 * (i % F::R3));
-}
-
 template <typename T, int LOGN>
 __device__ __forceinline__ void se_fill_t2(cx<T> *t2, const cx<T> *__restrict__ tab, int tid)
 {
@@ -296,13 +285,14 @@ inline unsigned cdiv(long a, long b) { return (unsigned)((a + b - 1) / b); }
     default: return hipErrorInvalidValue; \
     }
 
-// Pairs of energies a builder block walks: its twiddles and band rows (in L2) serve
-// them all.  Fixed by the axis alone, so that a batch takes one value for all its
-// instances (2048^2 x 512: 0.70 ms at 1, 0.63 at 4, 0.66 at 8).
+// Pairs of energies a builder block of rows walks: up to four, whose twiddles and band
+// rows (in L2) then serve them all (2048^2 x 512: 0.70 ms at 1, 0.63 at 4, 0.66 at 8), as
+// long as 2048 blocks remain (4096 x 256 x 8 slices: 33 us at 4, 17 at 1).  Results do
+// not depend on it.
 template <typename T, int LOGN>
-int se1_jc()
+int se1_jc(long blocks, long pairs)
 {
-    return LOGN >= 11 ? 4 : 1;
+    return LOGN >= 11 ? (int)std::max(1L, std::min(4L, blocks * pairs / 2048)) : 1;
 }
 
 // Slices of 1 GB and more in all, four times the last-level cache, are stored past
@@ -325,8 +315,9 @@ hipError_t se1_t(const Plan &pl, T *spec, int band, int acc, hipStream_t st)
 #define LH_SE1(LG)                                                                                                   \
     do {                                                                                                             \
         constexpr int L = se_lines<T, LG>(), GR = L < 4 ? 4 / L : 1;                                                 \
-        const int jc = se1_jc<T, LG>();                                                                              \
-        const dim3 grid(cdiv(cdiv(g.Hy, L), 8 * GR) * 8 * GR, cdiv(pairs, jc));                                \
+        const unsigned nx = cdiv(cdiv(g.Hy, L), 8 * GR) * 8 * GR;                                                    \
+        const int jc = se1_jc<T, LG>(nx, pairs);                                                                     \
+        const dim3 grid(nx, cdiv(pairs, jc));                                                                        \
         constexpr bool P = LG >= 11; /* shorter axes: plain stores only */                                          \
         const bool past = P && se_past(g, g.nS);                                                                     \
         const auto k = pl.rho ? (past ? &k_se1<T, LG, true, P> : &k_se1<T, LG, true, false>)                         \
@@ -355,12 +346,6 @@ hipError_t secol_t(const Plan &pl, T *spec, int n, bool inv, hipStream_t st)
         hipLaunchKernelGGL(k, grid, dim3(se_threads<T, LG>()), (se_lds<T, LG>(true)), st, spec, g,                   \
                            (const cx<T> *)pl.evy);                                                            \
     } while (0)
-    if constexpr (sizeof(T) == 8) {
-        if (g.logNy == 9) {
-            LH_SEC(9);
-            return hipGetLastError();
-        }
-    }
     LH_SE_SWITCH(g.logNy, LH_SEC)
 #undef LH_SEC
     return hipGetLastError();
@@ -378,8 +363,9 @@ hipError_t se_group_t(const Plan *const *pls, int n, const EvenInst *d, int pass
 #define LH_SE1(LG)                                                                                                   \
     do {                                                                                                             \
         constexpr int L = se_lines<T, LG>(), GR = L < 4 ? 4 / L : 1;                                                 \
-        const int jc = se1_jc<T, LG>();                                                                              \
-        const dim3 grid(cdiv(cdiv(g.Hy, L), 8 * GR) * 8 * GR, cdiv((m + 1) / 2, jc), n);                       \
+        const unsigned nx = cdiv(cdiv(g.Hy, L), 8 * GR) * 8 * GR;                                                    \
+        const int jc = se1_jc<T, LG>(nx, (long)n * ((m + 1) / 2));                                                   \
+        const dim3 grid(nx, cdiv((m + 1) / 2, jc), n);                                                               \
         const auto k = pls[0]->rho ? &k_se1_batch<T, LG, true> : &k_se1_batch<T, LG, false>;                         \
         hipLaunchKernelGGL(k, grid, dim3(se_threads<T, LG>()), (se_lds<T, LG>(false)), st, d, jc);                   \
     } while (0)
@@ -393,19 +379,37 @@ hipError_t se_group_t(const Plan *const *pls, int n, const EvenInst *d, int pass
         hipLaunchKernelGGL(k, dim3(cdiv(g.NTe, TB), m, n), dim3(se_threads<T, LG>()), (se_lds<T, LG>(true)), \
                            st, d);                                                                               \
     } while (0)
-        if constexpr (sizeof(T) == 8) {
-        if (g.logNy == 9) {
-            LH_SEC(9);
-            return hipGetLastError();
-        }
-    }
-    LH_SE_SWITCH(g.logNy, LH_SEC)
+        LH_SE_SWITCH(g.logNy, LH_SEC)
 #undef LH_SEC
     }
     return hipGetLastError();
 }
 
 }  // namespace
+
+// Rows of 1024 and 2048 points take it from 512 blocks on (two per CU), and from 16
+// blocks of rows, so that the last one's missing rows cost little: with fewer the full
+// transform's smaller blocks are faster (1024^2, us, FP32: 2 slices 8.9 against 10.5,
+// 8 slices 14.2 against 15.9, 32 slices 30.6 against 23.3; FP64 11.3 and 14.0, 21.6
+// and 22.6, 51.8 and 37.8; 512 slices of 33 rows: 1024 x 64 FP32 28.5 and 30.0, 2048 x 64
+// FP64 83 and 92; of 129 rows: 1024 x 256 FP32 70 and 56, 2048 x 256 FP64 267 and 237).
+bool se_rows(const Geo &g)
+{
+    if (!se_axis_x(g)) return false;
+    if (g.logNx >= 12) return true;
+    const int R3 = 1 << (g.logNx - 8), L = (g.fp64 || R3 < 8 ? 32 : 64) / R3;
+    return g.Hy >= 16 * L && (long)cdiv(g.Hy, L) * ((g.nS + 1) / 2) >= 512;
+}
+// Columns: FP32 always (64 x 1024 x 1 slice 7.7 and 7.9 us, 1024^2 x 64 33 and 29).  In
+// FP64 the full transform is faster at 512 and 1024 points (512^2 x 64 24.6 us against
+// 27.4, 1024^2 x 256 243 against 256), and at 2048 with less than 128 blocks (256 x
+// 2048, 4 slices 10.4 and 11.8 us, 16 slices 18.8 and 17.2, 256 slices 128 and 116).
+bool se_cols(const Geo &g, int n)
+{
+    if (!se_axis_y(g)) return false;
+    // (2048 points in FP64: four lines, so two tiles, to a block)
+    return !g.fp64 || g.logNy >= 12 || (long)cdiv(g.NTe, 2) * n >= 128;
+}
 
 hipError_t launch_se_group(const Plan *const *pls, int n, const EvenInst *d, int pass, hipStream_t st)
 {

@@ -133,7 +133,7 @@ struct Plan {
     void *twx = nullptr;       // cx<T>[nkx]
     void *twy = nullptr;       // cx<T>[nky]
     void *twz = nullptr;       // cx<T>[nkz] (three dimensions)
-    void *evx = nullptr, *evy = nullptr;  // EvenFFT twiddles of the axes (se_rows, se_cols)
+    void *evx = nullptr, *evy = nullptr;  // EvenFFT twiddles of the axes (se_axis_x, se_axis_y)
     // grids of any size: per axis chirp b, chirp spectra hf / hi, FFT twiddles of length M
     // (even path: chirp, spectrum and twiddles in EvenFFT's order)
     void *bsx[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -239,11 +239,13 @@ size_t even_any_spectrum_len(int logM);
 size_t even_any_spectrum_index(int logM, size_t e);
 size_t even_any_twiddle_len(int logM);
 size_t even_any_twiddle_index(int logM, size_t e);
-// The even path's passes on EvenFFT (lh_even_pow2.hip): P1 of one band, P2 / P4
-// over n slices, and the rules that choose them (the sizes from which they
-// measured faster).
-inline bool se_rows(const Geo &g) { return g.even && !g.bs && g.logNx >= 10; }
-inline bool se_cols(const Geo &g) { return g.even && !g.bs && g.logNy >= (g.fp64 ? 9 : 10); }
+// The even path's passes on EvenFFT (lh_even_pow2.hip): the axes that may take it
+// (their tables are held), and whether P1 of one band and a column pass over n
+// slices do.
+inline bool se_axis_x(const Geo &g) { return g.even && !g.bs && g.logNx >= 10; }
+inline bool se_axis_y(const Geo &g) { return g.even && !g.bs && g.logNy >= (g.fp64 ? 11 : 10); }
+bool se_rows(const Geo &g);
+bool se_cols(const Geo &g, int n);
 // The even path's transforms of small square grids, a slice per block
 // (lh_even_small.hip): P1 + P2 of one band (not added to another), P4 + P5.  Up to 128 points, as
 // far as a slice and its lines fit in LDS; faster at every size there.

@@ -2355,6 +2355,12 @@ static void launch_e1(const Plan &pl, T *spec, int band, int acc, hipStream_t st
                            pl.deps, pl.p.gamma, (const cx<T> *)pl.twx, spec, (const T *)nullptr, acc);
 }
 
+// Even column passes on the full transform (the others: se_cols)
+template <typename T>
+constexpr bool ecol_has(int logn)
+{
+    return logn <= (sizeof(T) == 4 ? 9 : 11);
+}
 template <typename T, int LOGN, bool INV>
 static void launch_ecol(const Plan &pl, T *spec, int nslices, hipStream_t st)
 {
@@ -2382,8 +2388,8 @@ static void launch_e5(const Plan &pl, const T *spec, int nplanes, T *out, int on
                        onx, ony, m2, acc);
 }
 
-// Up to 512 points (the even builder and columns; longer axes: se_rows, se_cols)
-#define LH_SWITCH_LOG9(v, CALL)                  \
+// Up to 2048 points (the even builder and columns; longer axes: se_rows, se_cols)
+#define LH_SWITCH_LOG11(v, CALL)                 \
     switch (v) {                                 \
     case 2: CALL(2); break;                      \
     case 3: CALL(3); break;                      \
@@ -2393,6 +2399,8 @@ static void launch_e5(const Plan &pl, const T *spec, int nplanes, T *out, int on
     case 7: CALL(7); break;                      \
     case 8: CALL(8); break;                      \
     case 9: CALL(9); break;                      \
+    case 10: CALL(10); break;                    \
+    case 11: CALL(11); break;                    \
     default: return hipErrorInvalidValue;        \
     }
 
@@ -2586,7 +2594,7 @@ static hipError_t exec_t(const Plan &pl, T *out, hipStream_t st, hipEvent_t *ev)
         if (se_rows(g)) return launch_se1(pl, dst, band, acc, st);
         if (g.even) {
 #define LH_E1(LG) launch_e1<T, LG>(pl, (T *)dst, band, acc, st)
-            LH_SWITCH_LOG9(g.logNx, LH_E1)
+            LH_SWITCH_LOG11(g.logNx, LH_E1)
 #undef LH_E1
         } else {
             for (int z = 0; z < g.nkz; ++z) {
@@ -2600,15 +2608,27 @@ static hipError_t exec_t(const Plan &pl, T *out, hipStream_t st, hipEvent_t *ev)
     };
     // forward (P2) or inverse (P4) column pass over n slices of buf
     auto col = [&](void *buf, int n, bool inv) -> hipError_t {
-        if (se_cols(g)) return launch_secol(pl, buf, n, inv, st);
+        if (se_cols(g, n)) return launch_secol(pl, buf, n, inv, st);
         if (g.even) {
             if (inv) {
-#define LH_E4(LG) launch_ecol<T, LG, true>(pl, (T *)buf, n, st)
-                LH_SWITCH_LOG9(g.logNy, LH_E4)
+#define LH_E4(LG)                                                          \
+    do {                                                                   \
+        if constexpr (ecol_has<T>(LG))                                     \
+            launch_ecol<T, LG, true>(pl, (T *)buf, n, st);                 \
+        else                                                               \
+            return hipErrorInvalidValue;                                   \
+    } while (0)
+                LH_SWITCH_LOG11(g.logNy, LH_E4)
 #undef LH_E4
             } else {
-#define LH_E2(LG) launch_ecol<T, LG, false>(pl, (T *)buf, n, st)
-                LH_SWITCH_LOG9(g.logNy, LH_E2)
+#define LH_E2(LG)                                                          \
+    do {                                                                   \
+        if constexpr (ecol_has<T>(LG))                                     \
+            launch_ecol<T, LG, false>(pl, (T *)buf, n, st);                 \
+        else                                                               \
+            return hipErrorInvalidValue;                                   \
+    } while (0)
+                LH_SWITCH_LOG11(g.logNy, LH_E2)
 #undef LH_E2
             }
         } else {
@@ -2886,8 +2906,9 @@ std::string even_group_key(const Plan &pl)
         g.e3_variant == 1)
         return std::string();
     char b[96];
-    std::snprintf(b, sizeof b, "e%d %d %d r%d s%d w%d %d", g.fp64, g.logNx, g.logNy, pl.rho ? 1 : 0, g.sw, g.e3_variant,
-                  g.e3_variant == 2 ? 16 : g.e3_TR);
+    const int se = se_rows(g) + 2 * se_cols(g, g.nS) + 4 * se_cols(g, g.nL);  // the passes' transforms
+    std::snprintf(b, sizeof b, "e%d %d %d r%d s%d t%d w%d %d", g.fp64, g.logNx, g.logNy, pl.rho ? 1 : 0, g.sw, se,
+                  g.e3_variant, g.e3_variant == 2 ? 16 : g.e3_TR);
     return b;
 }
 
@@ -2955,13 +2976,15 @@ static hipError_t even_group_t(const Plan *const *pls, int n, const EvenInst *d,
     } else if (se_rows(g)) {
         LH_HIP_TRY(launch_se_group(pls, n, d, 1, st));
     } else {
-        LH_SWITCH_LOG9(g.logNx, LH_E1B)
+        LH_SWITCH_LOG11(g.logNx, LH_E1B)
     }
 #undef LH_E1B
     // P2 / P4
     auto col = [&](int ns, bool inv) -> hipError_t {
 #define LH_ECB(LG)                                                                                                  \
-    do {                                                                                                            \
+    if constexpr (!ecol_has<T>(LG)) {                                                                               \
+        return hipErrorInvalidValue;                                                                                \
+    } else {                                                                                                        \
         using F = RegFFT<T, LG, false, ilog2_c(kEcolElems)>;                                                       \
         constexpr int C = sizeof(T) == 4 ? 4 : 2;                                                                   \
         constexpr int TPB = (F::G * C >= 256) ? 1 : 256 / (F::G * C);                                               \
@@ -2971,9 +2994,10 @@ static hipError_t even_group_t(const Plan *const *pls, int n, const EvenInst *d,
             hipLaunchKernelGGL((k_ecol_batch<T, LG, true>), grid, dim3(F::G * TPB * C), lds, st, d);                \
         else                                                                                                        \
             hipLaunchKernelGGL((k_ecol_batch<T, LG, false>), grid, dim3(F::G * TPB * C), lds, st, d);               \
-    } while (0)
-        if (se_cols(g)) return launch_se_group(pls, n, d, inv ? 4 : 2, st);
-        LH_SWITCH_LOG9(g.logNy, LH_ECB)
+    }
+        // (the instances of a group agree: even_group_key)
+        if (se_cols(g, inv ? g.nL : g.nS)) return launch_se_group(pls, n, d, inv ? 4 : 2, st);
+        LH_SWITCH_LOG11(g.logNy, LH_ECB)
 #undef LH_ECB
         return hipGetLastError();
     };
