@@ -299,8 +299,9 @@ int se1_jc(long blocks, long pairs)
 // the caches: the next pass starts at their beginning, which is evicted by then
 // either way, and the pass's own reads stay.  2048^2 x 512 x 256, ms: builder
 // 0.64 -> 0.61, P2 0.76 -> 0.71, P4 0.43 -> 0.42, FP64 1.44 -> 1.41, 1.48 -> 1.40 and 0.86 ->
-// 0.83.  A call with 134 MB of slices (2048^2, 16 lags) would go 259 -> 274 us, one with
-// 0.5 GB of FP64 ones 973 -> 997.
+// 0.83; 1024^2 x 1024 FP32 0.27 -> 0.28 and 0.36 -> 0.30, 1024 x 2048 x 600 P2 0.53 -> 0.50.
+// A call with 134 MB of slices (2048^2, 16 lags) would go 259 -> 274 us, one with 0.5 GB
+// of FP64 ones 973 -> 997.
 inline bool se_past(const Geo &g, int slices)
 {
     return (size_t)slices * g.slice_e * (g.fp64 ? 8 : 4) >= (size_t)1 << 30;
@@ -318,10 +319,9 @@ hipError_t se1_t(const Plan &pl, T *spec, int band, int acc, hipStream_t st)
         const unsigned nx = cdiv(cdiv(g.Hy, L), 8 * GR) * 8 * GR;                                                    \
         const int jc = se1_jc<T, LG>(nx, pairs);                                                                     \
         const dim3 grid(nx, cdiv(pairs, jc));                                                                        \
-        constexpr bool P = LG >= 11; /* shorter axes: plain stores only */                                          \
-        const bool past = P && se_past(g, g.nS);                                                                     \
-        const auto k = pl.rho ? (past ? &k_se1<T, LG, true, P> : &k_se1<T, LG, true, false>)                         \
-                              : (past ? &k_se1<T, LG, false, P> : &k_se1<T, LG, false, false>);                      \
+        const bool past = se_past(g, g.nS);                                                                          \
+        const auto k = pl.rho ? (past ? &k_se1<T, LG, true, true> : &k_se1<T, LG, true, false>)                      \
+                              : (past ? &k_se1<T, LG, false, true> : &k_se1<T, LG, false, false>);                   \
         hipLaunchKernelGGL(k, grid, dim3(se_threads<T, LG>()), (se_lds<T, LG>(false)), st, pl.xi + band * nk, g,     \
                            pl.p.emin, pl.deps, pl.p.gamma, (const cx<T> *)pl.evx, spec,                              \
                            pl.rho ? (const T *)pl.rho + band * nk : nullptr, acc, jc);                               \
@@ -339,10 +339,9 @@ hipError_t secol_t(const Plan &pl, T *spec, int n, bool inv, hipStream_t st)
     do {                                                                                                             \
         constexpr int TB = se_lines<T, LG>() / (16 / (int)sizeof(T));                                                \
         const dim3 grid(cdiv(g.NTe, TB), n);                                                                         \
-        constexpr bool P = LG >= 11; /* shorter axes: plain stores only */                                          \
-        const bool past = P && se_past(g, n);                                                                        \
-        const auto k = inv ? (past ? &k_secol<T, LG, true, P> : &k_secol<T, LG, true, false>)                        \
-                           : (past ? &k_secol<T, LG, false, P> : &k_secol<T, LG, false, false>);                     \
+        const bool past = se_past(g, n);                                                                             \
+        const auto k = inv ? (past ? &k_secol<T, LG, true, true> : &k_secol<T, LG, true, false>)                     \
+                           : (past ? &k_secol<T, LG, false, true> : &k_secol<T, LG, false, false>);                  \
         hipLaunchKernelGGL(k, grid, dim3(se_threads<T, LG>()), (se_lds<T, LG>(true)), st, spec, g,                   \
                            (const cx<T> *)pl.evy);                                                            \
     } while (0)
