@@ -608,8 +608,12 @@ __global__ void __launch_bounds__(kThreads) k_p5(const cx<T> *__restrict__ spec,
                             a += o.x;
                             b += o.y;
                         }
+                        // (read back by the next pair, as in e5_body)
+                        *reinterpret_cast<cx<T> *>(orow + X) = mk<T>(a, b);
+                        asm volatile("");
+                    } else {
+                        store_past<(LOGL >= 9)>(reinterpret_cast<cx<T> *>(orow + X), mk<T>(a, b));
                     }
-                    store_past<(LOGL >= 9)>(reinterpret_cast<cx<T> *>(orow + X), mk<T>(a, b));
                 }
             }
         }
@@ -1554,8 +1558,14 @@ __device__ __forceinline__ void e5_body(const T *__restrict__ spec, const Geo &g
                                 // a band pair's |M(Q)|^2 map, the pairs summed in the output
                                 val = (T)((double)val * (double)m2[(size_t)Y * out_nx + X]);
                                 if (acc) val += orow[X];
+                                // (read back by the next pair: not past the caches.  The
+                                // empty asm keeps the compiler from merging the two stores
+                                // into a plain one.)
+                                orow[X] = val;
+                                asm volatile("");
+                            } else {
+                                store_past<(LOGNX >= 10)>(orow + X, val);
                             }
-                            store_past<(LOGNX >= 10)>(orow + X, val);
                         }
                     }
                 }
