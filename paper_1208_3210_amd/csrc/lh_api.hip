@@ -343,16 +343,18 @@ lindhard_status plan_describe(const lindhard_problem *p, Plan &pl)
     // mirror symmetry of the band -> real even transforms on the quarter plane
     {
         bool sym = true;
-        // a table (band or momentum density) must be mirror symmetric bit for bit
+        // a table (band or momentum density) must be mirror symmetric bit for bit: the
+        // rows up to ny / 2 along x, and equal to the rows ny - iy (whole rows at a time,
+        // no early exit inside, so that the compiler makes vector code of them)
         auto mirror = [&](const double *tab) {
             const int nx = p->nkx, ny = p->nky;
-            for (int iy = 0; iy < ny; ++iy)
-                for (int ix = 0; ix < nx; ++ix) {
-                    const double e = tab[(size_t)iy * nx + ix];
-                    if (e != tab[(size_t)iy * nx + (ix ? nx - ix : 0)] ||
-                        e != tab[(size_t)(iy ? ny - iy : 0) * nx + ix])
-                        return false;
-                }
+            for (int iy = 0; iy <= ny / 2; ++iy) {
+                const double *row = tab + (size_t)iy * nx, *mir = tab + (size_t)((ny - iy) % ny) * nx;
+                int bad = 0;
+                for (int ix = 1; 2 * ix < nx; ++ix) bad |= row[ix] != row[nx - ix];
+                for (int ix = 0; ix < nx; ++ix) bad |= row[ix] != mir[ix];
+                if (bad) return false;
+            }
             return true;
         };
         if (nkz > 1) sym = false;  // the real even form: two dimensions
@@ -371,11 +373,17 @@ lindhard_status plan_describe(const lindhard_problem *p, Plan &pl)
         // (FP32; LINDHARD_SYMMETRY=exchange takes it from 16 on)
         const char *sym_env = std::getenv("LINDHARD_SYMMETRY");
         bool exch = p->nkx == p->nky && p->nkx >= (sym_env && !std::strcmp(sym_env, "exchange") ? 16 : 128);
+        // (a mirror-symmetric table's quarter, in squares of 32 points that stay in the L1)
         auto exchanged = [&](const double *tab) {
-            const int n = p->nkx;
-            for (int iy = 0; iy <= n / 2; ++iy)
-                for (int ix = 0; ix < iy; ++ix)
-                    if (tab[(size_t)iy * n + ix] != tab[(size_t)ix * n + iy]) return false;
+            const int n = p->nkx, h = n / 2 + 1;
+            for (int y0 = 0; y0 < h; y0 += 32)
+                for (int x0 = 0; x0 <= y0; x0 += 32) {
+                    int bad = 0;
+                    for (int iy = y0; iy < std::min(h, y0 + 32); ++iy)
+                        for (int ix = x0; ix < std::min(h, x0 + 32); ++ix)
+                            bad |= tab[(size_t)iy * n + ix] != tab[(size_t)ix * n + iy];
+                    if (bad) return false;
+                }
             return true;
         };
         for (int b = 0; b < nbands && sym && exch; ++b) {
