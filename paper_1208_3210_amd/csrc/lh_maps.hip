@@ -34,7 +34,7 @@ struct MapArgs {
     int ff, kzn;
     double ffs, V;
     const double2 *ffx, *ffy;
-    int logtx, nseg, wb, zc;
+    int logtx, nseg, wb, zc, g0;
 };
 
 // VEC consecutive values: one 16-byte access (or one element).
@@ -73,7 +73,7 @@ __global__ void __launch_bounds__(256) k_map(const T *__restrict__ im1, const T 
     // of first-zone rows (kz plane outermost)
     const int it = blockIdx.x;
     const int zi = it % a.zy, rest = it / a.zy, seg = rest % a.nseg;
-    const int r = rest / a.nseg * (256 >> a.logtx) + ((int)threadIdx.x >> a.logtx);  // row of nkz x nky
+    const int r = (a.g0 + rest / a.nseg) * (256 >> a.logtx) + ((int)threadIdx.x >> a.logtx);  // row of nkz x nky
     const int xu = ((seg << a.logtx) + (threadIdx.x & ((1 << a.logtx) - 1))) * VEC;  // column within a zone
     if (r >= a.nky * a.nkz || xu >= a.nkx) return;
     const int Zc = r / a.nky, yv = r - Zc * a.nky, zr = a.zy * a.nky, Yb = zi * a.nky + yv, Y = Zc * zr + Yb;
@@ -114,8 +114,7 @@ __global__ void __launch_bounds__(256) k_map(const T *__restrict__ im1, const T 
         const int m = a.lags[w];
         const double f = a.fracs[w];
         const bool ina = m >= 1 && m < a.neps, inb = m + 1 >= 1 && m + 1 < a.neps;
-                MV im = map_load<T, VEC>(im1 + (size_t)(ina ? m : 1) * nk + q), re;
-
+        MV im = map_load<T, VEC>(im1 + (size_t)(ina ? m : 1) * nk + q), re;
         if (!ina) {
 #pragma unroll
             for (int i = 0; i < VEC; ++i) im.v[i] = (T)0;
@@ -129,8 +128,7 @@ __global__ void __launch_bounds__(256) k_map(const T *__restrict__ im1, const T 
         if constexpr (RPA) {
             // Re chi at the omega: its lag's plane, or the blend of two lags
             const int sa = a.kkslot[2 * w], sb = a.kkslot[2 * w + 1];
-                        re = map_load<T, VEC>(re1 + (size_t)sa * nk + q);
-
+            re = map_load<T, VEC>(re1 + (size_t)sa * nk + q);
             if (f > 0.0 && sb >= 0) {
                 const MV y = map_load<T, VEC>(re1 + (size_t)sb * nk + q);
 #pragma unroll
@@ -207,19 +205,24 @@ hipError_t map_t(const Plan &pl, bool rpa, T *im, int vkind, double V, T *re, T 
     const int rpb = 256 >> a.logtx, nz = (pl.zx + gmax - 1) / gmax;
     a.zc = (pl.zx + nz - 1) / nz;
     const int zc = a.zc == 1 ? 1 : a.zc <= 3 ? 3 : 5;
-    const int nblk = (g.nky * g.nkz + rpb - 1) / rpb * a.nseg * pl.zy;
+    const int groups = (g.nky * g.nkz + rpb - 1) / rpb, per = a.nseg * pl.zy;  // of rows; blocks of one
+    const long nblk = (long)groups * per;
     // omegas per block: 16 for one array and 8 for three (each measured best at
     // 128 omegas: 16 gives 0.61 / 1.89 ms, 8 gives 0.66 / 1.84), fewer while that
     // leaves less than two blocks per CU
     a.wb = rpa ? 8 : 16;
-    while (a.wb > 1 && (long)nblk * nz * ((a.nw + a.wb - 1) / a.wb) < 512) a.wb /= 2;
+    while (a.wb > 1 && nblk * nz * ((a.nw + a.wb - 1) / a.wb) < 512) a.wb /= 2;
     while ((a.nw + a.wb - 1) / a.wb > 65535) a.wb *= 2;
-    const dim3 grid(nblk, (a.nw + a.wb - 1) / a.wb, nz);
+    // at most 2^19 blocks along x in one launch (a launch takes 2^32 threads there)
+    const int gl = std::max(1, (1 << 19) / per);
     const auto go = [&](auto vc, auto zcc) {
         constexpr int VC = decltype(vc)::value, ZC = decltype(zcc)::value;
         const auto k = !rpa ? &k_map<T, VC, ZC, false, false>
                             : vkind == 1 ? &k_map<T, VC, ZC, true, true> : &k_map<T, VC, ZC, true, false>;
-        hipLaunchKernelGGL(k, grid, dim3(256), 0, st, (const T *)pl.im1, (const T *)pl.re1, a, im, re, imr, rer);
+        for (a.g0 = 0; a.g0 < groups; a.g0 += gl) {
+            const dim3 grid(std::min(gl, groups - a.g0) * per, (a.nw + a.wb - 1) / a.wb, nz);
+            hipLaunchKernelGGL(k, grid, dim3(256), 0, st, (const T *)pl.im1, (const T *)pl.re1, a, im, re, imr, rer);
+        }
     };
     using I1 = std::integral_constant<int, 1>;
     using I3 = std::integral_constant<int, 3>;

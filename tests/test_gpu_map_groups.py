@@ -27,3 +27,18 @@ def test_groups(nkx, nky, zones, prec):
         plan.close()
     for a, b in zip(*maps):
         assert torch.equal(a, b[:len(few)])
+
+
+def test_rows_beyond_one_launch():
+    """More than 2^19 blocks of rows (three dimensions, 16383 zones along y): every zone
+    image equals the map of one zone."""
+    nkx, nky, nkz, zy = 8, 4, 256, 16383
+    eps = np.random.Generator(np.random.PCG64(4)).uniform(-0.8, 0.8, size=(nkz, nky, nkx))
+    kw = dict(eps_table=eps, nkz=nkz, mu=0.1, nkx=nkx, nky=nky, neps=8, emin=-1.6, emax=1.6, gamma=0.2,
+              omega=[0.8], want_rpa=True, precision=LH.LINDHARD_FP32C)
+    one, many = LH.Plan(**kw), LH.Plan(zones=(1, zy), **kw)
+    for a, b in zip([one.exec()] + list(one.rpa(0.8)), [many.exec()] + list(many.rpa(0.8))):
+        a = a.reshape(nkz, 1, nky, nkx)
+        assert torch.equal(b.reshape(nkz, zy, nky, nkx), a.expand(nkz, zy, nky, nkx))
+    one.close()
+    many.close()
