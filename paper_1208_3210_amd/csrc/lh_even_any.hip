@@ -56,11 +56,7 @@ constexpr int ev_threads()
 // Pairs of energies a block of the builder takes side by side: more of them share
 // the band values, fewer leave longer pieces of the 128-byte lines to a block
 // (2049^2 x 512: 3.07 ms with one, 2.89 with two, 3.56 with four).
-template <typename T, int LOGM>
-constexpr int ev_pairs()
-{
-    return 2;
-}
+constexpr int kEvPairs = 2;
 // LDS values between lines: the row passes run consecutive lanes along one
 // line; the column passes interleave the lines lane by lane, so there the line
 // starts are spread over the banks (32 or 8 consecutive slots are served at once).
@@ -184,7 +180,7 @@ __global__ void __launch_bounds__((ev_threads<T, LOGM>()), (sizeof(T) == 4 ? 6 :
 {
     using F = EvenFFT<T, LOGM>;
     constexpr int L = ev_lines<T, LOGM>(), NT = ev_threads<T, LOGM>(), LS = ev_stride<T, LOGM>(false);
-    constexpr int LP = ev_pairs<T, LOGM>(), LR = L / LP;
+    constexpr int LP = kEvPairs, LR = L / LP;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cx<T> *lds = reinterpret_cast<cx<T> *>(smem_raw), *t2 = lds + L * LS;
     const int tid = threadIdx.x, line = tid / F::TL, q = tid % F::TL;
@@ -431,7 +427,7 @@ hipError_t pass_t(const Plan &pl, int pass, void *out, hipStream_t st)
 #define LH_BE1(LG)                                                                                                   \
     do {                                                                                                             \
         constexpr int L = ev_lines<T, LG>();                                                                         \
-        constexpr int LP = ev_pairs<T, LG>(), LR = L / LP, GR = LR < 4 ? 4 / LR : 1;                                 \
+        constexpr int LP = kEvPairs, LR = L / LP, GR = LR < 4 ? 4 / LR : 1;                                          \
         const unsigned nx = cdiv(cdiv(g.Hy, LR), 8 * GR) * 8 * GR;                                                   \
         const int jc = (int)std::max(1L, std::min(8L, (long)nx * pairs / LP / 2048));                                \
         const auto k = pl.rho ? &k_be1<T, LG, true> : &k_be1<T, LG, false>;                                          \
@@ -448,7 +444,7 @@ hipError_t pass_t(const Plan &pl, int pass, void *out, hipStream_t st)
         const unsigned nx = cdiv(g.NTe, TB);                                                                         \
         const int sj = (int)std::max(1L, std::min(4L, (long)nx * n / 2048));                                         \
         hipLaunchKernelGGL((k_becol<T, LG>), dim3(nx, cdiv(n, sj)), dim3(ev_threads<T, LG>()), (ev_lds<T, LG>(true)), \
-                           st, spec, g, ev_tab(pl, true), n, sj, pass == 2 && g.sw);                                                    \
+                           st, spec, g, ev_tab(pl, true), n, sj, pass == 2 && g.sw);                                 \
     } while (0)
         LH_EV_SWITCH(g.logMy, LH_BEC)
 #undef LH_BEC

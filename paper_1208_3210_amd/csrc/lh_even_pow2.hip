@@ -284,6 +284,17 @@ inline unsigned cdiv(long a, long b) { return (unsigned)((a + b - 1) / b); }
     case 12: CALL(12); break;             \
     default: return hipErrorInvalidValue; \
     }
+// columns (FP64 from 2048 points: se_axis_y)
+#define LH_SE_COLS(v, CALL)                     \
+    if constexpr (sizeof(T) == 4) {             \
+        LH_SE_SWITCH(v, CALL)                   \
+    } else {                                    \
+        switch (v) {                            \
+        case 11: CALL(11); break;               \
+        case 12: CALL(12); break;               \
+        default: return hipErrorInvalidValue;   \
+        }                                       \
+    }
 
 // Pairs of energies a builder block of rows walks: up to four, whose twiddles and band
 // rows (in L2) then serve them all (2048^2 x 512: 0.70 ms at 1, 0.63 at 4, 0.66 at 8), as
@@ -345,7 +356,7 @@ hipError_t secol_t(const Plan &pl, T *spec, int n, bool inv, hipStream_t st)
         hipLaunchKernelGGL(k, grid, dim3(se_threads<T, LG>()), (se_lds<T, LG>(true)), st, spec, g,                   \
                            (const cx<T> *)pl.evy);                                                            \
     } while (0)
-    LH_SE_SWITCH(g.logNy, LH_SEC)
+    LH_SE_COLS(g.logNy, LH_SEC)
 #undef LH_SEC
     return hipGetLastError();
 }
@@ -375,10 +386,9 @@ hipError_t se_group_t(const Plan *const *pls, int n, const EvenInst *d, int pass
     do {                                                                                                             \
         constexpr int TB = se_lines<T, LG>() / (16 / (int)sizeof(T));                                                \
         const auto k = pass == 4 ? &k_secol_batch<T, LG, true> : &k_secol_batch<T, LG, false>;                       \
-        hipLaunchKernelGGL(k, dim3(cdiv(g.NTe, TB), m, n), dim3(se_threads<T, LG>()), (se_lds<T, LG>(true)), \
-                           st, d);                                                                               \
+        hipLaunchKernelGGL(k, dim3(cdiv(g.NTe, TB), m, n), dim3(se_threads<T, LG>()), (se_lds<T, LG>(true)), st, d); \
     } while (0)
-        LH_SE_SWITCH(g.logNy, LH_SEC)
+        LH_SE_COLS(g.logNy, LH_SEC)
 #undef LH_SEC
     }
     return hipGetLastError();

@@ -76,7 +76,8 @@ struct EvenFFT {
     }
 
     // The length-P transform of row `row` by its threads t: v[i] = Z[j(i)].
-    // t2: the T2 table (LDS).  Contains block barriers.
+    // t2: the T2 table (LDS).  A row's threads are lanes of one wave: their exchange
+    // takes no block barrier.
     __device__ static __forceinline__ void fwd(cx<T> *v, cx<T> *row, const cx<T> *t2, int t)
     {
 #pragma unroll
