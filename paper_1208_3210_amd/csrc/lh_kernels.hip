@@ -478,6 +478,7 @@ __global__ void __launch_bounds__(kThreads) k_p3(cx<T> *__restrict__ spec, Geo g
 // MODE 0: plane = requested omega; writes the extended, form-factor weighted
 //         map out[plane][Y][X] (zeros for an empty window).
 // MODE 1: plane = window slot; writes the first-zone map out[m][qy][qx].
+// MODE 2: as 0, times a band pair's |M(Q)|^2 map m2, added to the output if acc.
 template <typename T, int LOGL, int MODE>
 __global__ void __launch_bounds__(kThreads) k_p5(const cx<T> *__restrict__ spec, Geo g,
                                                 const cx<T> *__restrict__ twx, const PlaneSrc *__restrict__ psrc,
@@ -500,11 +501,11 @@ __global__ void __launch_bounds__(kThreads) k_p5(const cx<T> *__restrict__ spec,
     const int row = tid / G, gg = tid % G;
     const int plane = blockIdx.y;
     const int qy0 = blockIdx.x * R;
-    const PlaneSrc ps = MODE == 0 ? psrc[plane] : PlaneSrc{plane, -1, 1.0, 0.0};
+    const PlaneSrc ps = MODE != 1 ? psrc[plane] : PlaneSrc{plane, -1, 1.0, 0.0};
     const int slot = ps.a;
     const int nkx = g.nkx, nky = g.nky;
 
-    if (MODE == 0 && slot < 0) {
+    if (MODE != 1 && slot < 0) {
         if (acc) return;  // adds nothing
         for (int rz = 0; rz < R * zy; ++rz) {
             const int r = rz % R, zi = rz / R;
@@ -583,7 +584,7 @@ __global__ void __launch_bounds__(kThreads) k_p5(const cx<T> *__restrict__ spec,
 
     const T sc = (T)scale;
     const int qy = qy0 + row;
-    if (MODE == 0) {
+    if (MODE != 1) {
         for (int zi = 0; zi < zy; ++zi) {
             const int Y = zi * nky + ((qy + zy * nky / 2) & (nky - 1));
             T *orow = out + ((size_t)plane * out_ny + Y) * out_nx;
@@ -598,7 +599,7 @@ __global__ void __launch_bounds__(kThreads) k_p5(const cx<T> *__restrict__ spec,
                         a = (T)((double)a * form_factor_sq(ffx[X], fy, ffs));
                         b = (T)((double)b * form_factor_sq(ffx[X + 1], fy, ffs));
                     }
-                    if (m2) {
+                    if constexpr (MODE == 2) {
                         // a band pair's |M(Q)|^2 map, the pairs summed in the output
                         const cx<T> mm = *reinterpret_cast<const cx<T> *>(m2 + (size_t)Y * out_nx + X);
                         a = (T)((double)a * (double)mm.x);
@@ -608,12 +609,9 @@ __global__ void __launch_bounds__(kThreads) k_p5(const cx<T> *__restrict__ spec,
                             a += o.x;
                             b += o.y;
                         }
-                        // (read back by the next pair, as in e5_body)
-                        *reinterpret_cast<cx<T> *>(orow + X) = mk<T>(a, b);
-                        asm volatile("");
-                    } else {
-                        store_past<(LOGL >= 9)>(reinterpret_cast<cx<T> *>(orow + X), mk<T>(a, b));
                     }
+                    // (MODE 2: read back by the next pair, not past the caches)
+                    store_past<(LOGL >= 9 && MODE == 0)>(reinterpret_cast<cx<T> *>(orow + X), mk<T>(a, b));
                 }
             }
         }
@@ -1430,7 +1428,7 @@ __global__ void __launch_bounds__(kThreads, 4) k_e3m(T *__restrict__ spec, Geo g
 // the full even row rebuilt from rx in [0, nkx/2]; its FFT gives the two real
 // rows C(qx, qy) for every qx, written to rows qy and nky - qy of each zone.
 // MODE 0: extended, form-factor weighted output planes; MODE 1: first-zone
-// planes (natural order) for the RPA path.
+// planes (natural order) for the RPA path; MODE 2: as 0 with a band pair's map.
 template <typename T, int LOGNX, int MODE>
 __device__ __forceinline__ void e5_body(const T *__restrict__ spec, const Geo &g, const cx<T> *__restrict__ twx,
                                                 const PlaneSrc *__restrict__ psrc, double scale, int zx, int zy,
@@ -1451,12 +1449,12 @@ __device__ __forceinline__ void e5_body(const T *__restrict__ spec, const Geo &g
     const int line = tid / G, gg = tid % G;
     const int plane = blockIdx.y;
     const int p0 = blockIdx.x * R;
-    const PlaneSrc ps = MODE == 0 ? psrc[plane] : PlaneSrc{plane, -1, 1.0, 0.0};
+    const PlaneSrc ps = MODE != 1 ? psrc[plane] : PlaneSrc{plane, -1, 1.0, 0.0};
     const int slot = ps.a;
     const int nkx = g.nkx, nky = g.nky, Hy = g.Hy, H = N / 2, SW = H + 1;
     const int rows = 2 * R, logRows = 1 + __builtin_ctz(R);
 
-    if (MODE == 0 && slot < 0) {
+    if (MODE != 1 && slot < 0) {
         if (acc) return;  // adds nothing
         for (int rz = 0; rz < rows * 2 * zy; ++rz) {
             const int r = rz % rows, mir = (rz / rows) & 1, zi = rz / (2 * rows);
@@ -1542,7 +1540,7 @@ __device__ __forceinline__ void e5_body(const T *__restrict__ spec, const Geo &g
         for (int mir = 0; mir < 2; ++mir) {
             const int qy = mir ? (nky - qy0) & (nky - 1) : qy0;
             if (mir && qy == qy0) continue;
-            if (MODE == 0) {
+            if (MODE != 1) {
                 for (int zi = 0; zi < zy; ++zi) {
                     const int Y = zi * nky + ((qy + zy * nky / 2) & (nky - 1));
                     T *orow = out + ((size_t)plane * out_ny + Y) * out_nx;
@@ -1554,18 +1552,13 @@ __device__ __forceinline__ void e5_body(const T *__restrict__ spec, const Geo &g
                             const int X = zj * nkx + ((qx + nkx / 2) & (nkx - 1));
                             T val = (half ? v[s].y : v[s].x) * sc;
                             if (ff) val = (T)((double)val * form_factor_sq(ffx[X], fy, ffs));
-                            if (m2) {
+                            if constexpr (MODE == 2) {
                                 // a band pair's |M(Q)|^2 map, the pairs summed in the output
                                 val = (T)((double)val * (double)m2[(size_t)Y * out_nx + X]);
                                 if (acc) val += orow[X];
-                                // (read back by the next pair: not past the caches.  The
-                                // empty asm keeps the compiler from merging the two stores
-                                // into a plain one.)
-                                orow[X] = val;
-                                asm volatile("");
-                            } else {
-                                store_past<(LOGNX >= 10)>(orow + X, val);
                             }
+                            // (MODE 2: read back by the next pair, not past the caches)
+                            store_past<(LOGNX >= 10 && MODE == 0)>(orow + X, val);
                         }
                     }
                 }
@@ -2675,7 +2668,11 @@ static hipError_t exec_t(const Plan &pl, T *out, hipStream_t st, hipEvent_t *ev)
                 LH_SWITCH_LOG12(g.logNx, LH_E5)
 #undef LH_E5
             } else {
-#define LH_E5(LG) launch_e5<T, LG, 0>(pl, spr, pl.p.nomega, out, pl.out_nx, pl.out_ny, st, m2, acc)
+#define LH_E5(LG)                                                                             \
+    if (m2)                                                                                   \
+        launch_e5<T, LG, 2>(pl, spr, pl.p.nomega, out, pl.out_nx, pl.out_ny, st, m2, acc);    \
+    else                                                                                      \
+        launch_e5<T, LG, 0>(pl, spr, pl.p.nomega, out, pl.out_nx, pl.out_ny, st)
                 LH_SWITCH_LOG12(g.logNx, LH_E5)
 #undef LH_E5
             }
@@ -2696,7 +2693,11 @@ static hipError_t exec_t(const Plan &pl, T *out, hipStream_t st, hipEvent_t *ev)
                 for (int z = 0; z < g.nkz; ++z) {
                     const cx<T> *sz = spec + (size_t)z * g.plane_elems;
                     T *oz = out + (size_t)((z + g.nkz / 2) & (g.nkz - 1)) * pl.zy * g.nky * pl.out_nx;
-#define LH_P5(LG) launch_p5<T, LG, 0>(pl, sz, pl.p.nomega, oz, pl.out_nx, pl.out_ny, st, m2, acc)
+#define LH_P5(LG)                                                                             \
+    if (m2)                                                                                   \
+        launch_p5<T, LG, 2>(pl, sz, pl.p.nomega, oz, pl.out_nx, pl.out_ny, st, m2, acc);      \
+    else                                                                                      \
+        launch_p5<T, LG, 0>(pl, sz, pl.p.nomega, oz, pl.out_nx, pl.out_ny, st)
                     LH_SWITCH_LOG(g.logL, LH_P5)
 #undef LH_P5
                 }
