@@ -242,8 +242,8 @@ __global__ void __launch_bounds__((ev_threads<T, LOGM>()), (sizeof(T) == 4 ? 6 :
 // a wave's loads and stores cover whole tile rows.  In place, one slice at a
 // time for sj slices, streamed past the L1, which holds the tables (2.96 -> 2.47
 // ms at 2049^2 x 512).  upper: only the rows ry >= Ce tile are stored (the forward
-// pass with the exchange symmetry).  The padding columns (rx > nkx / 2) are taken as
-// zero (see ecol_body).
+// pass with the exchange symmetry).  The padding columns (rx > nkx / 2) need no mask
+// here: there is one band, and its builder writes them as zeros in every call.
 template <typename T, int LOGM>
 __global__ void __launch_bounds__((ev_threads<T, LOGM>()), (sizeof(T) == 4 ? 6 : 3))
     k_becol(T *__restrict__ spec, Geo g, EvTab ty, int nslices, int sj, int upper)
@@ -257,8 +257,7 @@ __global__ void __launch_bounds__((ev_threads<T, LOGM>()), (sizeof(T) == 4 ? 6 :
     const int line = tid % L, q = tid / L;                 // first pass
     const int line2 = tid / F::TL, q2 = tid % F::TL;       // length-P transforms
     const int tile = blockIdx.x * (L / C) + line / C, c = line % C;
-    const int rx = tile * g.Ce + 2 * c;  // first column of the pair
-    const bool act = q <= F::P / 2 && tile < g.NTe && rx <= g.L;
+    const bool act = q <= F::P / 2 && tile < g.NTe;
     const int H = g.nky / 2, nlo = upper ? tile * g.Ce : 0;
     ev_fill_t2<T, LOGM>(t2, ty, tid);
     const int s0 = blockIdx.y * sj, s1 = min(nslices, s0 + sj);
@@ -271,9 +270,7 @@ __global__ void __launch_bounds__((ev_threads<T, LOGM>()), (sizeof(T) == 4 ? 6 :
         for (int i = 0; i < kNz; ++i) {
             const int n = ev_index<F::P>(i, qo);
             const bool in = act && n <= H;
-            cx<T> z0 = load_nt(at32(base, o0 + (in ? n : 0) * C));
-            if (rx + 1 > g.L) z0.y = (T)0;
-            x[i] = cmul(z0, ev_chirp<T>(ty, n, in));
+            x[i] = cmul(load_nt(at32(base, o0 + (in ? n : 0) * C)), ev_chirp<T>(ty, n, in));
         }
         ev_convolve<T, LOGM>(x, lds + line * LS, lds + line2 * LS, t2, ty, qo, act, q2 + z);
         if (act) {
@@ -314,17 +311,17 @@ __global__ void __launch_bounds__((ev_threads<T, LOGM>()), (sizeof(T) == 4 ? 6 :
     // zone images [im0, im1) of nzx columns of images
     const int nzx = MODE == 0 ? zx : 1, nim = MODE == 0 ? zx * zy : 1;
     const int per = (nim + (int)gridDim.z - 1) / (int)gridDim.z;
-    const int im0 = (int)blockIdx.z * per, im1 = min(nim, im0 + per);
+    const int im0 = (int)blockIdx.z * per, im1 = min(nim, im0 + per), zi0 = im0 / nzx, zj0 = im0 - zi0 * nzx;
     const int sx = MODE == 0 ? (zx * nkx) / 2 % nkx : 0, sy = MODE == 0 ? (zy * nky) / 2 % nky : 0;
     const size_t oplane = (size_t)(MODE == 0 ? plane : g.m_lo + plane) * ony;
     if (MODE == 0 && ps.a < 0) {  // the plane is zero (block-uniform)
         for (int r = 0; r < 2 * L && row0 + r < Hy; ++r)
             for (int mir = 0; mir < 2; ++mir) {
                 const int qy = mir ? (nky - (row0 + r)) % nky : row0 + r;
-                for (int im = im0; im < im1; ++im) {
-                    const int zi = im / nzx, zj = im - zi * nzx;
+                for (int im = im0, zi = zi0, zj = zj0; im < im1; ++im) {
                     T *orow = out + (oplane + zi * nky + (qy + sy) % nky) * onx + (size_t)zj * nkx;
                     for (int X = tid; X < nkx; X += NT) orow[X] = (T)0;
+                    if (++zj == nzx) zj = 0, ++zi;
                 }
             }
         return;
@@ -370,8 +367,8 @@ __global__ void __launch_bounds__((ev_threads<T, LOGM>()), (sizeof(T) == 4 ? 6 :
             const int qy = mir ? (nky - qy0) % nky : qy0;
             if (mir && qy == qy0) continue;
             const int yv = (qy + sy) % nky;
-            for (int im = im0; im < im1; ++im) {
-                const int zi = im / nzx, zj = im - zi * nzx, Y = zi * nky + yv;
+            for (int im = im0, zi = zi0, zj = zj0; im < im1; ++im) {
+                const int Y = zi * nky + yv;
                 T *orow = out + (oplane + Y) * onx;
                 const double2 fy = MODE == 0 && ff ? ffy[Y] : make_double2(1.0, 0.0);
                 const int qo = q + opaque_zero();
@@ -392,6 +389,7 @@ __global__ void __launch_bounds__((ev_threads<T, LOGM>()), (sizeof(T) == 4 ? 6 :
                         if (n > 0 && 2 * n != nkx) orow[xb] = val;
                     }
                 }
+                if (++zj == nzx) zj = 0, ++zi;
             }
         }
     }
