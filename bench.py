@@ -29,7 +29,9 @@ KERNEL_NAMES = ["k_p1", "k_col<float, false>", "k_p3", "k_col<float, true>", "k_
 
 
 def window_half(cfg):
-    """Share of the points the even path's window works on (exchange symmetry)."""
+    """Share of the points the even path's window works on: half of them where the
+    library uses the exchange symmetry of the tight-binding band (square grids of 128
+    points and more)."""
     return 0.5 if cfg["nkx"] == cfg["nky"] and cfg["nkx"] >= 128 else 1.0
 
 

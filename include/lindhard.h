@@ -184,7 +184,9 @@ lindhard_status lindhard_exec(lindhard_plan_t plan, void *im_chi, void *stream);
  * the five passes (P1 spectral builder + row FFT, P2 column FFT, P3 energy
  * window, P4 inverse column FFT, P5 inverse row FFT + epilogue), waits for
  * the last one and writes the five durations in milliseconds to pass_ms[0..4]
- * (host array).  Synchronous.  Errors: EINVAL, EDEVICE. */
+ * (host array).  On square grids of 16 to 128 points with a mirror-symmetric band
+ * one kernel does P1 and P2 and one P4 and P5: their times stand at P1 and P5.
+ * Synchronous.  Errors: EINVAL, EDEVICE. */
 lindhard_status lindhard_exec_timed(lindhard_plan_t plan, void *im_chi, void *stream, float *pass_ms);
 
 /* After lindhard_exec on a plan built with want_rpa: Kramers-Kronig real part

@@ -359,7 +359,10 @@ lindhard_status plan_describe(const lindhard_problem *p, Plan &pl)
         };
         if (nkz > 1) sym = false;  // the real even form: two dimensions
         // sizes that are not powers of two: even convolutions of at most 4096
-        // points (sizes up to 2049; longer lines would not fit twice in a CU's LDS)
+        // points (sizes up to 2049; longer lines would not fit twice in a CU's LDS).
+        // No lower line: against the complex passes, whose transforms are shorter
+        // than the least of 256 points here, us a call at 64 energies x 16 lags: 5^2 FP32
+        // 54 -> 39, FP64 51 -> 46; 17^2 111 -> 39, 117 -> 44; 33^2 109 -> 40; 65^2 145 -> 42
         const int evx = std::max(8, ilog2(4 * (p->nkx / 2))), evy = std::max(8, ilog2(4 * (p->nky / 2)));
         if (g.bs && (evx > 12 || evy > 12)) sym = false;
         for (int b = 0; b < nbands && sym; ++b) {
