@@ -38,8 +38,9 @@ __device__ __forceinline__ double form_factor_sq(const double2 fx, const double2
 // the caches, which then keep the spectra that the pass reads, from rows of 1024
 // points on (two bands 1024^2 x 129 lags: 171 -> 144 us for the pass, 2048^2 x 256 FP64:
 // 2.20 -> 2.14 ms, 1024 x 512 x 128 with a caller's band: 130 -> 117; at 512^2 x 64 a
-// call takes 93 and 95 us, at 256^2 x 64 with 3 x 3 zones 69 and 94).  Builder and
-// column passes store large spectra so (se_past).
+// call takes 93 and 95 us, at 256^2 x 64 with 3 x 3 zones 69 and 94).  Not the pair maps,
+// which the next pair reads back (1024^2 x 16 lags x 4 pairs, a call 559 -> 528 us).
+// Builder and column passes store large spectra so (se_past).
 template <bool NT, typename T>
 __device__ __forceinline__ void store_past(T *p, T v)
 {

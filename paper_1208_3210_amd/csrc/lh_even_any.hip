@@ -18,8 +18,9 @@
 // 2049^2 points x 512 energies x 256 lags with momentum density, FP32, against
 // the full complex Bluestein passes (ms): P1 16.7 -> 2.9, P2 11.1 -> 2.3, window
 // 7.3 -> 0.6, P4 5.7 -> 1.2, P5 9.7 -> 2.1; a call 50.6 -> 9.1.  300 x 257 x 128 x 64
-// in FP64: 0.66 -> 0.19.  Bound by the vector units (55 - 70 % busy) and the
-// latency of the exchanges at eighteen waves per CU.
+// in FP64: 0.66 -> 0.19.  Bound by the vector units (59 - 68 % busy) and the
+// latency of the exchanges at eighteen waves per CU; 300 x 257 in FP64 by that latency
+// alone (vector units 14 - 22 % busy, blocks of 4.5 waves).
 #include <algorithm>
 
 #include "lh_device.h"

@@ -7,7 +7,7 @@
 // 2048^2 x 512 x 256, ms: builder 0.86 -> 0.63, P2 0.90 -> 0.80, P4 0.47 -> 0.46 in
 // FP32, 2.00 -> 1.43, 1.76 -> 1.47 and 0.95 -> 0.87 in FP64; at 4096^2, FP32, 4.5 ->
 // 2.7, 4.8 -> 3.1 and 2.8 -> 1.8; at 1024^2, FP32, 0.26 -> 0.16, 0.24 -> 0.18 and 0.13 ->
-// 0.10.  The builder is bound by the vector units (73 % busy), the columns by HBM.  The
+// 0.10.  The builder is bound by the vector units (75 % busy), the columns by HBM.  The
 // last row pass on the same transform (mirrored stores from the butterflies) took 1.8 ms
 // against 1.0 and is not kept.
 #include <algorithm>
